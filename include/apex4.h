@@ -169,9 +169,9 @@ int apex4_w4a4_gemm_debug(const uint8_t* A_q, const void* s_a,
 #define APEX4_ENTRY_GEMM_WS 1 /* apex4_w4a4_gemm_ws (and _debug with workspace) */
 #define APEX4_ENTRY_LINEAR 2  /* apex4_w4a4_linear (and _debug); its GEMM, after the quantizer */
 #define APEX4_ENTRY_LINEAR_WS 3 /* apex4_w4a4_linear_ws; its GEMM, after the quantizer */
-#define APEX4_KERNEL_GEMV 1       /* one row (two on tiled weights): v_dot8 on the packed codes */
-#define APEX4_KERNEL_FUSED 2      /* one row: quantizer fused into the GEMV's prologue */
-#define APEX4_KERNEL_DECODE 3     /* up to 32 rows: weights streamed once through the MFMA */
+#define APEX4_KERNEL_GEMV 1       /* one row (tiled weights: two): v_dot8 on the packed codes */
+#define APEX4_KERNEL_FUSED 2      /* one row: quantizer fused into the GEMM's prologue */
+#define APEX4_KERNEL_DECODE 3     /* few rows (below 256): K split over the waves of a workgroup, no barrier in the loop */
 #define APEX4_KERNEL_TILE_64 4    /* 64 x 128 output tiles */
 #define APEX4_KERNEL_TILE_128 5   /* 128 x 256 output tiles */
 #define APEX4_KERNEL_PINGPONG 6   /* G = 128 or 256 on 128 x 256 tiles, MFMA and dequant waves alternating */
@@ -180,7 +180,9 @@ int apex4_w4a4_gemm_debug(const uint8_t* A_q, const void* s_a,
 /*
  * The GEMM kernel that `entry` runs for this shape on the current device, and
  * its split over K (*splits = S > 1 only for APEX4_ENTRY_GEMM_WS and
- * APEX4_ENTRY_LINEAR_WS, whose workspace size query then returns S M N 4 bytes).  flags as in
+ * APEX4_ENTRY_LINEAR_WS, whose workspace size query then returns S M N 4 bytes;
+ * APEX4_KERNEL_DECODE adds its parts inside the workgroups and leaves that
+ * workspace unused).  flags as in
  * apex4_w4a4_gemm_debug (APEX4_DEBUG_W_TILED: the tiled entry points;
  * APEX4_ENTRY_LINEAR and APEX4_ENTRY_LINEAR_WS take no APEX4_DEBUG_GENERAL_TILES).  M == 0 gives kernel 0,
  * splits 0.  Shape and group rules as apex4_w4a4_gemm; unknown entry or flags:
@@ -302,10 +304,11 @@ int apex4_w4a4_linear_debug(const void* x, const uint8_t* W_q, const void* s_w,
  * whole tiles, the remaining tiles' 128-wide K stages are spread evenly over
  * the workgroups, and a tile cut between workgroups has its fp32 parts added in
  * segment order by the workgroup that finishes last (counters cleared by a
- * kernel on every call, so a captured call replays).  Y is then within the
- * tolerance of apex4_w4a4_gemm (the fp32 summation order differs; for G == K
- * the tile kernels' split gives the same bits), deterministic for a given shape
- * and device.
+ * kernel on every call, so a captured call replays).  Where the few-row kernel
+ * of apex4_w4a4_gemm (fewer than 256 rows) is faster than either, it runs and
+ * leaves the workspace unused.  Y is within the tolerance of apex4_w4a4_gemm
+ * (the fp32 summation order differs; for G == K the split over K gives the
+ * same bits), deterministic for a given shape and device.
  *
  * apex4_w4a4_gemm_workspace_size writes to *bytes the workspace this shape
  * needs on the current device: S * M * N * 4 for the split over K, counters

@@ -53,7 +53,7 @@ hipError_t launch_quantize(const uint16_t* x, int64_t M, int64_t K, int64_t G,
 enum GemmKernel : int {
     kKernelGemv = 1,      // one row, v_dot8 on the packed codes
     kKernelFused = 2,     // one row, quantize in the prologue (linear only)
-    kKernelDecode = 3,    // up to 32 rows, weights streamed once
+    kKernelDecode = 3,    // few rows, weights streamed once
     kKernelTile64 = 4,    // 64 x 128 tiles, 4 waves (K may split inside the workgroup)
     kKernelTile128 = 5,   // 128 x 256 tiles, 8 waves
     kKernelPingPong = 6,  // G = 128 on 128 x 256 tiles, ping-pong schedule
@@ -104,6 +104,8 @@ bool decode_fits(int64_t M, int64_t N, int64_t K, int64_t G);
 // through the workspace in a fixed order (decode_split_workspace_bytes is 0
 // where it does not apply).
 int64_t decode_split_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t G);
+// Whether that form is also the faster one (the workspace stays required).
+bool decode_split_pays(int64_t M, int64_t N, int64_t K, int64_t G);
 hipError_t launch_gemm_decode(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq,
                               const uint16_t* sw, int64_t M, int64_t N, int64_t K, int64_t G,
                               uint16_t* Y, hipStream_t stream, Dump dump = Dump(), bool wt = false,
@@ -116,6 +118,22 @@ bool gemv_fits(int64_t M, int64_t N, int64_t K, int64_t G, bool wt = false);
 hipError_t launch_gemv(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw, int64_t M,
                        int64_t N, int64_t K, int64_t G, uint16_t* Y, hipStream_t stream, Dump dump = Dump(),
                        bool wt = false);
+
+// W4A4 GEMM for few rows (below kRowsMax) at G >= 128 or per channel: K split
+// over the waves of a workgroup, no barrier in the loop.  rows_cost_us: its
+// time for more than 32 rows on 256 CUs, for the choice against the tile
+// kernels.  rows_fused: the one-row linear on tiled weights with the quantizer
+// in the prologue (codes and scales also to Aq / sa); Y as launch_quantize
+// followed by launch_gemm_rows gives, bit for bit.
+constexpr int64_t kRowsMax = 256;
+bool rows_fits(int64_t M, int64_t N, int64_t K, int64_t G);
+double rows_cost_us(int64_t M, int64_t N, int64_t K, int64_t G);
+hipError_t launch_gemm_rows(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw, int64_t M,
+                            int64_t N, int64_t K, int64_t G, uint16_t* Y, hipStream_t stream, Dump dump = Dump(),
+                            bool wt = false);
+bool rows_fused_fits(int64_t M, int64_t N, int64_t K, int64_t G);
+hipError_t launch_rows_fused(const uint16_t* x, const uint8_t* Wt, const uint16_t* sw, int64_t N, int64_t K, int64_t G,
+                             uint16_t* Y, uint8_t* Aq, uint16_t* sa, hipStream_t stream, Dump dump = Dump());
 
 // Quantize + W4A4 GEMM in one kernel: the one-row kernel above, quantizing x
 // in its prologue (G in {32, 64, 128, 256, 512}, G < K).  Y as

@@ -1247,14 +1247,53 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t stream)
     return hipGetLastError();
 }
 
+namespace {
+
+// Time in us of the tile kernels on 256 CUs at G = 128 for fewer than kRowsMax
+// rows, split S ways over K (the planes' bytes are written and read): least
+// squares over 343 shapes of 40 .. 250 rows, N = 1024 .. 28672, K = 1024 ..
+// 28672 on MI355X, within 30 % of each.
+// Per channel: 190 shapes.
+double tile_cost_us(int64_t M, int64_t N, int64_t K, bool ch, int S) {
+    const int64_t cus = device_cu_count();
+    const double n = static_cast<double>(kstages(K));
+    const double mbytes = 1e-6 * S * static_cast<double>(M * N * 4);
+    if (S > 1) return ch ? 5.5 + 0.464 * n / S + 0.89 * mbytes : 8.4 + 1.08 * n / S + 0.36 * mbytes;
+    const int64_t big = ((M + 127) / 128) * ((N + 255) / 256), small = ((M + 63) / 64) * ((N + 127) / 128);
+    const double rounds = static_cast<double>(((big >= cus ? big : small) + cus - 1) / cus);
+    if (big >= cus) return 4.0 + (ch ? 0.9 : 1.25) * n * rounds;
+    if (ch) return rounds == 1.0 ? 5.1 + 0.27 * n : 3.2 + rounds * (1.3 + 0.262 * n);
+    return rounds == 1.0 ? 4.7 + 0.4 * n : 1.5 + rounds * (1.8 + 0.429 * n);
+}
+
+// More than 32 rows: the few-row kernel, where it is the faster one.  Over the
+// shapes above (tiled weights past the cache) it is 1.48 times as fast as the
+// tile kernels on average, choosing by these costs loses 0.4 % against the
+// faster of the two (64 rows, N = K = 8192: 14 against 23 us split over K;
+// N = 57344: 69 against 76; 128 rows: 20 against 29; but 250 rows, N = 28672,
+// K = 1024: 28 against 22 on 64 x 128 tiles).
+bool rows_take(int64_t M, int64_t N, int64_t K, int64_t G, int S) {
+    return rows_fits(M, N, K, G) && (M <= 32 || rows_cost_us(M, N, K, G) < tile_cost_us(M, N, K, G == K, S));
+}
+
+}  // namespace
+
+// One row (row-major weights), or two (tiled): the dot-product kernel.  Up to
+// 32 rows: the few-row kernels (G >= 128 or per channel: the one of
+// gemm_w4a4_rows.hip; finer groups, and the stream-K form of the workspace
+// path: the persistent one).  Below kRowsMax rows: the few-row kernel or the
+// tile kernels by cost; the few-row kernel splits K over the waves of a
+// workgroup and leaves the workspace unused, whose size (splits) stays that of
+// the tile kernels' split.
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G, bool split, bool force_tile, bool wt) {
-    if (split) {
-        const int S = splitk_factor(M, N, K, G);
-        if (S > 1) return {G == 128 && !force_tile ? kKernelPingPong : kKernelTile64, S};
+    const int S = split ? splitk_factor(M, N, K, G) : 1;
+    if (!force_tile) {
+        if (gemv_fits(M, N, K, G, wt)) return {kKernelGemv, 1};
+        if (split && !gemv_fits(M, N, K, G) && decode_split_pays(M, N, K, G)) return {kKernelDecodeSplit, 1};
+        if (rows_take(M, N, K, G, S)) return {kKernelDecode, S};
+        if (decode_fits(M, N, K, G)) return {kKernelDecode, 1};
     }
-    if (!force_tile && gemv_fits(M, N, K, G, wt)) return {kKernelGemv, 1};
-    if (!force_tile && decode_fits(M, N, K, G))
-        return {split && decode_split_workspace_bytes(M, N, K, G) > 0 ? kKernelDecodeSplit : kKernelDecode, 1};
+    if (S > 1) return {G == 128 && !force_tile ? kKernelPingPong : kKernelTile64, S};
     const int64_t big_tiles = ((M + 127) / 128) * ((N + 255) / 256);
     if (big_tiles < device_cu_count()) return {kKernelTile64, 1};
     return {(G == 128 || G == 256) && !force_tile ? kKernelPingPong : kKernelTile128, 1};
@@ -1267,7 +1306,9 @@ hipError_t launch_planned(const GemmPlan& plan, const uint8_t* Aq, const uint16_
                           hipStream_t stream, Dump dump, float* part, bool wt) {
     switch (plan.kernel) {
         case kKernelGemv: return launch_gemv(Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, wt);
-        case kKernelDecode: return launch_gemm_decode(Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, wt);
+        case kKernelDecode:
+            return rows_fits(M, N, K, G) ? launch_gemm_rows(Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, wt)
+                                         : launch_gemm_decode(Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, wt);
         case kKernelDecodeSplit: return launch_gemm_decode(Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, wt, part);
         case kKernelTile64:
             return launch_tiles<4, 2>(Aq, sa, Wq, sw, M, N, K, G, Y, dump, wt, stream, plan.splits, part);
@@ -1288,7 +1329,8 @@ hipError_t launch_gemm_splitk(const uint8_t* Aq, const uint16_t* sa, const uint8
     const GemmPlan plan = plan_gemm(M, N, K, G, true, force_tile, wt);
     if (plan.kernel == kKernelDecodeSplit)  // the workspace holds the stream-K counters and parts
         return launch_planned(plan, Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, part, wt);
-    if (plan.splits < 2) return launch_planned(plan, Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, nullptr, wt);
+    if (plan.splits < 2 || plan.kernel == kKernelDecode)
+        return launch_planned(plan, Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, nullptr, wt);
     const int S = plan.splits;
     // split ranges hold whole groups, so every group sum except the
     // per-channel one is dumped by the kernel that completes it
@@ -1307,9 +1349,8 @@ hipError_t launch_gemm_splitk(const uint8_t* Aq, const uint16_t* sa, const uint8
     return launch_splitk_reduce(part, S, M * N, Y, stream);
 }
 
-// One row (two on tiled weights): the dot-product kernel; up to 32 rows: the
-// weight-streaming kernel; otherwise the tile kernels (the same choice with or
-// without a dump).
+// The kernel of plan_gemm without a workspace (the same choice with or without
+// a dump).
 hipError_t launch_gemm(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw,
                        int64_t M, int64_t N, int64_t K, int64_t G, uint16_t* Y, hipStream_t stream, Dump dump,
                        bool force_tile, bool wt) {

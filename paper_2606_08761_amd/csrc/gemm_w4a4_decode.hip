@@ -663,9 +663,12 @@ hipError_t launch_decode_pf(const uint8_t* Aq, const uint16_t* sa, const uint8_t
     const int64_t wave_stages = sk.grid ? (tiles * kstages(K) / sk.grid + NWAVE - 1) / NWAVE
                                         : (tiles + cus - 1) / cus * ((K / 128 + NWAVE - 1) / NWAVE);
     const bool alds = !TAIL && wave_stages >= 16 && decode_alds(M, K, G);
+    // one group per stage or more: only the stream-K form (the rest is
+    // launch_gemm_rows)
+    if (GPS == 1 && !sk.grid) return hipErrorInvalidValue;
 #define APEX4_DECODE_SK(R, A)                                                                                          \
     return sk.grid ? launch_decode_k<R, PF, GPS, DUMP, TAIL, A, true>(Aq, sa, Wq, sw, M, N, K, G, Y, dump, wt, stream, sk) \
-                   : launch_decode_k<R, PF, GPS, DUMP, TAIL, A, false>(Aq, sa, Wq, sw, M, N, K, G, Y, dump, wt, stream, sk)
+                   : launch_decode_k<R, PF, GPS, DUMP, TAIL, A, GPS == 1>(Aq, sa, Wq, sw, M, N, K, G, Y, dump, wt, stream, sk)
 #define APEX4_DECODE_ROWS(R)                                                                                           \
     if (alds) { APEX4_DECODE_SK(R, !TAIL); }                                                                           \
     APEX4_DECODE_SK(R, false)
@@ -717,6 +720,18 @@ bool decode_fits(int64_t M, int64_t N, int64_t K, int64_t G) {
 
 int64_t decode_split_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t G) {
     return decode_fits(M, N, K, G) ? decode_sk_plan(M, N, K, G).bytes : 0;
+}
+
+// At G >= 128 or per channel the form competes with the kernel of
+// gemm_w4a4_rows.hip, which keeps several workgroups per CU: it is kept for few
+// tiles of many stages, and for a few tiles past one full round (MI355X, 16
+// rows, K = 28672, us: N = 1024 12.6 against 14.0, but N = 2560 19.0 against
+// 18.8, N = 5120 26.9 against 20.7, N = 12288 46.6 against 40.6, N = 28672
+// 92.8 against 79.7).
+bool decode_split_pays(int64_t M, int64_t N, int64_t K, int64_t G) {
+    if (decode_split_workspace_bytes(M, N, K, G) == 0) return false;
+    const int64_t tiles = (N + COLS - 1) / COLS, cus = device_cu_count();
+    return (G < 128 && G != K) || tiles <= cus / 4 || (tiles > cus && tiles - cus <= cus / 8);
 }
 
 hipError_t launch_gemm_decode(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw,

@@ -27,18 +27,12 @@
 //     instead of its codes and quantizes it into LDS in the prologue with the
 //     quantizer's own arithmetic (quant_core.h: same codes and scales, bit for
 //     bit); workgroup 0 also writes them to the caller's work buffers.
-//   * Tiled weights (w4a4_gemv_tiled_kernel): W in the tiled layout
-//     (apex4_internal.h), where a 1 KB run holds 16 bytes of each of 32 rows:
-//     a workgroup takes one 32-row tile and its 8 waves split the tile's 1 KB
-//     runs; lanes l and l + 32 hold the same row, so a row's sum is one
-//     shuffle, then the waves' partials are added in a fixed order in LDS.
-//   * Two rows (tiled weights, R = 2): every weight run is multiplied with
-//     both activation rows (both in LDS), so the weights are still read once;
-//     the VALU work doubles.  Measured on MI355X against the MFMA few-row
-//     kernel at M = 2 (tiled weights, rotated, graph replay): 7-12 % faster at
-//     N = 10240 and 28672 or K = 28672, even at N = K = 8192; at M = 3..4 the
-//     four-row form was 5-17 % slower and at M = 8 40-55 %, so only M = 2
-//     takes it.
+//   * Two rows on tiled weights (w4a4_gemv_tiled_kernel; apex4_internal.h has
+//     the layout), where a 1 KB run holds 16 bytes of each of 32 rows: a
+//     workgroup takes one 32-row tile and its 8 waves split the tile's 1 KB
+//     runs; every run is multiplied with both activation rows (both in LDS).
+//     Lanes l and l + 32 hold the same row, so a row's sum is one shuffle,
+//     then the waves' partials are added in a fixed order in LDS.
 //   * DUMP (rows [pm0, pm0 + pmr) of the R): every lane's exact 32-code partial
 //     sum is added with an integer atomic into the zeroed P[pmr][N][K/G],
 //     giving the exact group sums whatever the order; sa == nullptr (codes
@@ -216,27 +210,25 @@ __global__ __launch_bounds__(GV_NT) void w4a4_gemv_kernel(
 
 constexpr int GT_WAVES = 8;  // tiled: waves per workgroup (one 32-row tile)
 constexpr int GT_NT = 64 * GT_WAVES;
-constexpr int GT_MAX_LDS = 128 * 1024 + 1024;  // dynamic LDS of the tiled kernel (the static part is 1 KB)
+constexpr int GT_MAX_LDS = 128 * 1024 + 1024;  // dynamic LDS of the tiled kernel (the static part is 2 KB)
 constexpr int GT_SWP = 16;                      // weight scales per thread loaded ahead (K/G <= 256 in full)
 
-// One row against tiled weights.  Workgroup t owns rows 32 t .. 32 t + 31; its
+// Two rows against tiled weights.  Workgroup t owns rows 32 t .. 32 t + 31; its
 // wave w takes the tile's 1 KB runs q = w, w + GT_WAVES, ... (run q = stage
 // q / 2, half q % 2), GV_LOADS at a time; lane l holds row 32 t + l % 32 and the
 // 32 codes at packed bytes 64 (q / 2) + 32 (l / 32) + 16 (q % 2).  G >= 128, so
 // a run lies in one group, g = 128 (q / 2) / G for every lane: the tile's
 // weight scales are staged in LDS group-major ([K/G][32], one coalesced pass)
 // and a run reads 32 consecutive ones.
-// R activation rows (1, or 2 without FUSE): A rows r at gv_lds + r K/32,
-// their scales at sa_lds + r K/G; rows past M repeat row M - 1 (never stored).
-template <bool FUSE, int QL, bool DUMP, int R = 1>
+// R activation rows: A rows r at gv_lds + r K/32, their scales at
+// sa_lds + r K/G; rows past M repeat row M - 1 (never stored).
+template <bool DUMP, int R>
 __global__ __launch_bounds__(GT_NT) void w4a4_gemv_tiled_kernel(
     const uint8_t* __restrict__ Aq, const uint16_t* __restrict__ sa, const uint8_t* __restrict__ Wt,
     const uint16_t* __restrict__ sw, int M, int N, int K, int G, int lgG, uint16_t* __restrict__ Y,
-    const uint16_t* __restrict__ x, uint8_t* __restrict__ aq_out, uint16_t* __restrict__ sa_out,
     int32_t* __restrict__ P, int pm0, int pmr) {
-    static_assert(R == 1 || !FUSE, "the fused prologue quantizes one row");
     static_assert(R <= GT_WAVES, "one wave per output row in the final sum");
-    const bool have_sc = FUSE || !DUMP || sa != nullptr;  // uniform
+    const bool have_sc = !DUMP || sa != nullptr;  // uniform
     extern __shared__ uint4 gv_lds[];
     __shared__ float red[GT_WAVES][R][32];
     const int tid = threadIdx.x, lane = tid & 63, lh = lane >> 5;
@@ -278,19 +270,15 @@ __global__ __launch_bounds__(GT_NT) void w4a4_gemv_tiled_kernel(
     uint16_t swv[GT_SWP];
 #pragma unroll
     for (int u = 0; u < GT_SWP; ++u) swv[u] = tid + u * GT_NT < nsw ? sw_at(tid + u * GT_NT) : static_cast<uint16_t>(0);
-    if constexpr (R == 1) {
-        gv_stage_a<FUSE, QL, GT_NT>(gv_lds, sa_lds, Aq, sa, have_sc, K, ng, x, aq_out, sa_out);
-    } else {
-        for (int i = tid; i < R * kv; i += GT_NT) {
-            const int r = i / kv, c = i - r * kv;
-            gv_lds[i] = reinterpret_cast<const uint4*>(Aq + static_cast<int64_t>(min(r, M - 1)) * kb)[c];
-        }
-        if (have_sc)
-            for (int i = tid; i < R * ng; i += GT_NT) {
-                const int r = i / ng, g = i - r * ng;
-                sa_lds[i] = gv_h2f(sa[static_cast<int64_t>(min(r, M - 1)) * ng + g]);
-            }
+    for (int i = tid; i < R * kv; i += GT_NT) {
+        const int r = i / kv, c = i - r * kv;
+        gv_lds[i] = reinterpret_cast<const uint4*>(Aq + static_cast<int64_t>(min(r, M - 1)) * kb)[c];
     }
+    if (have_sc)
+        for (int i = tid; i < R * ng; i += GT_NT) {
+            const int r = i / ng, g = i - r * ng;
+            sa_lds[i] = gv_h2f(sa[static_cast<int64_t>(min(r, M - 1)) * ng + g]);
+        }
 #pragma unroll
     for (int u = 0; u < GT_SWP; ++u) {
         const int i = tid + u * GT_NT;
@@ -346,10 +334,8 @@ __global__ __launch_bounds__(GT_NT) void w4a4_gemv_tiled_kernel(
 }
 
 size_t gemv_lds_bytes(int64_t K, int64_t G) { return static_cast<size_t>(K / 2) + 4 * static_cast<size_t>(K / G); }
-// tiled, R rows: R rows of codes and scales plus the tile's weight scales, binary16 [K/G][32]
-size_t gemv_tiled_lds_bytes(int64_t K, int64_t G, int R = 1) {
-    return R * gemv_lds_bytes(K, G) + 64 * static_cast<size_t>(K / G);
-}
+// tiled, two rows: their codes and scales plus the tile's weight scales, binary16 [K/G][32]
+size_t gemv_tiled_lds_bytes(int64_t K, int64_t G) { return 2 * gemv_lds_bytes(K, G) + 64 * static_cast<size_t>(K / G); }
 
 // Rows per wave and workgroups: fill the load batch, but keep at least 8 waves
 // per CU when N allows.
@@ -366,42 +352,27 @@ GemvGrid gemv_grid(int64_t N, int64_t K) {
     return {rpw, (waves + GV_WAVES - 1) / GV_WAVES};
 }
 
-template <bool FUSE, int QL, int R = 1>
+int log2_group(int64_t K, int64_t G) {
+    int lg = 31;
+    if (G != K)
+        for (lg = 5; (int64_t{1} << lg) < G; ++lg) {
+        }
+    return lg;
+}
+
+// 32-code partial sums are added atomically into a zeroed window.
+hipError_t clear_dump(const Dump& dump, int64_t N, int64_t K, int64_t G, hipStream_t stream) {
+    return dump.P ? launch_fill_i32(dump.P, static_cast<int64_t>(dump.mr) * N * (K / G), 0, stream) : hipSuccess;
+}
+
+template <bool FUSE, int QL>
 hipError_t launch_gemv_t(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw, int64_t N,
                          int64_t K, int64_t G, uint16_t* Y, const uint16_t* x, uint8_t* aq_out, uint16_t* sa_out,
-                         Dump dump, bool wt, hipStream_t stream, int64_t M = 1) {
-    int lgG = 31;
-    if (G != K)
-        for (lgG = 5; (int64_t{1} << lgG) < G; ++lgG) {
-        }
+                         Dump dump, hipStream_t stream) {
     const size_t lds = gemv_lds_bytes(K, G);
-    const int n = static_cast<int>(N), k = static_cast<int>(K), g = static_cast<int>(G);
-    if (dump.P) {
-        // 32-code partial sums are added atomically into a zeroed window
-        const hipError_t e = launch_fill_i32(dump.P, static_cast<int64_t>(dump.mr) * N * (K / G), 0, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (wt) {
-        const dim3 gd(static_cast<unsigned>((N + 31) / 32)), bd(GT_NT);
-        const size_t lds_t = gemv_tiled_lds_bytes(K, G, R);
-        // above 64 KB of dynamic LDS the kernel must allow it (at most
-        // GT_MAX_LDS where the fits functions hold)
-        static std::atomic<uint64_t> lds_allowed[2] = {{0}, {0}};
-        const void* kf = dump.P ? reinterpret_cast<const void*>(w4a4_gemv_tiled_kernel<FUSE, QL, true, R>)
-                                : reinterpret_cast<const void*>(w4a4_gemv_tiled_kernel<FUSE, QL, false, R>);
-        const hipError_t ea = allow_dynamic_lds(kf, GT_MAX_LDS, lds_allowed[dump.P ? 1 : 0]);
-        if (ea != hipSuccess) return ea;
-        if (lds_t > GT_MAX_LDS) return hipErrorInvalidValue;
-        const int m = static_cast<int>(M);
-        if (dump.P)
-            hipLaunchKernelGGL((w4a4_gemv_tiled_kernel<FUSE, QL, true, R>), gd, bd, lds_t, stream, Aq, sa, Wq, sw, m, n,
-                               k, g, lgG, Y, x, aq_out, sa_out, dump.P, dump.m0, dump.mr);
-        else
-            hipLaunchKernelGGL((w4a4_gemv_tiled_kernel<FUSE, QL, false, R>), gd, bd, lds_t, stream, Aq, sa, Wq, sw, m,
-                               n, k, g, lgG, Y, x, aq_out, sa_out, static_cast<int32_t*>(nullptr), 0, 0);
-        return hipGetLastError();
-    }
-    if constexpr (R != 1) return hipErrorInvalidValue;  // several rows: tiled weights only
+    const int n = static_cast<int>(N), k = static_cast<int>(K), g = static_cast<int>(G), lgG = log2_group(K, G);
+    const hipError_t e = clear_dump(dump, N, K, G, stream);
+    if (e != hipSuccess) return e;
     const GemvGrid gg = gemv_grid(N, K);
     const dim3 gd(static_cast<unsigned>(gg.grid)), bd(GV_NT);
     const int rpw = static_cast<int>(gg.rpw);
@@ -414,53 +385,66 @@ hipError_t launch_gemv_t(const uint8_t* Aq, const uint16_t* sa, const uint8_t* W
     return hipGetLastError();
 }
 
-// Workgroups of a one-row launch (row-major: rows-per-wave grid; tiled: one per 32 rows).
-int64_t gemv_workgroups(int64_t N, int64_t K, bool wt) { return wt ? (N + 31) / 32 : gemv_grid(N, K).grid; }
+template <bool DUMP>
+hipError_t launch_gemv_tiled(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wt, const uint16_t* sw, int64_t M,
+                             int64_t N, int64_t K, int64_t G, uint16_t* Y, Dump dump, hipStream_t stream) {
+    const size_t lds = gemv_tiled_lds_bytes(K, G);
+    // above 64 KB of dynamic LDS the kernel must allow it
+    static std::atomic<uint64_t> lds_allowed{0};
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(w4a4_gemv_tiled_kernel<DUMP, 2>), GT_MAX_LDS, lds_allowed);
+    if (e != hipSuccess) return e;
+    e = clear_dump(dump, N, K, G, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((w4a4_gemv_tiled_kernel<DUMP, 2>), dim3(static_cast<unsigned>((N + 31) / 32)), dim3(GT_NT), lds, stream,
+                       Aq, sa, Wt, sw, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), static_cast<int>(G),
+                       log2_group(K, G), Y, dump.P, dump.m0, dump.mr);
+    return hipGetLastError();
+}
 
 }  // namespace
 
 bool gemv_fits(int64_t M, int64_t N, int64_t K, int64_t G, bool wt) {
     const bool g_ok = G == K || G == 32 || G == 64 || G == 128 || G == 256 || G == 512 || G == 1024;
-    if (M == 2)  // two rows: tiled weights (G >= 128), both rows in LDS
-        return wt && N >= 1 && g_ok && G >= 128 && gemv_tiled_lds_bytes(K, G, 2) <= GT_MAX_LDS;
+    if (wt)  // two rows, both in LDS (one row: the few-row kernel)
+        return M == 2 && N >= 1 && g_ok && G >= 128 && gemv_tiled_lds_bytes(K, G) <= GT_MAX_LDS;
     return M == 1 && N >= 1 && g_ok && gemv_lds_bytes(K, G) <= GV_MAX_LDS;
 }
 
 hipError_t launch_gemv(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw, int64_t M,
                        int64_t N, int64_t K, int64_t G, uint16_t* Y, hipStream_t stream, Dump dump, bool wt) {
-    if (!gemv_fits(M, N, K, G, wt) || (wt && G < 128)) return hipErrorInvalidValue;
-    if (M == 2)
-        return launch_gemv_t<false, 1, 2>(Aq, sa, Wq, sw, N, K, G, Y, nullptr, nullptr, nullptr, dump, wt, stream, M);
-    return launch_gemv_t<false, 1>(Aq, sa, Wq, sw, N, K, G, Y, nullptr, nullptr, nullptr, dump, wt, stream);
+    if (!gemv_fits(M, N, K, G, wt)) return hipErrorInvalidValue;
+    if (wt)
+        return dump.P ? launch_gemv_tiled<true>(Aq, sa, Wq, sw, M, N, K, G, Y, dump, stream)
+                      : launch_gemv_tiled<false>(Aq, sa, Wq, sw, M, N, K, G, Y, dump, stream);
+    return launch_gemv_t<false, 1>(Aq, sa, Wq, sw, N, K, G, Y, nullptr, nullptr, nullptr, dump, stream);
 }
 
 // Every workgroup quantizes all of x, so the fused prologue's total work is
 // (workgroups x K): up to 2^23 it is cheaper than a second launch (measured on
 // MI355X: 0.8 - 1.4 us faster at N = 1024 .. 10240, K = 8192), beyond it the
 // separate quantizer wins (0.9 us at N = 28672, 12 us at N = 8192, K = 28672).
+// (Tiled weights: rows_fused_fits.)
 constexpr int64_t GV_FUSE_WORK = int64_t{1} << 23;
-// Tiled weights: 8-wave workgroups, and the fused form only paid up to
-// 256 x 8192 (MI355X: about even at N = 8192, K = 8192; 10 us slower at
-// N = 10240 and 20 us at N = 28672 than the quantizer and the GEMM).
-constexpr int64_t GT_FUSE_WORK = int64_t{1} << 21;
 
 bool fused_linear_fits(int64_t M, int64_t N, int64_t K, int64_t G, bool wt) {
+    if (wt) return rows_fused_fits(M, N, K, G);
     return M == 1 && gemv_fits(M, N, K, G) && (G == 32 || G == 64 || G == 128 || G == 256 || G == 512) && G < K &&
-           !(wt && G < 128) && gemv_workgroups(N, K, wt) * K <= (wt ? GT_FUSE_WORK : GV_FUSE_WORK);
+           gemv_grid(N, K).grid * K <= GV_FUSE_WORK;
 }
 
 hipError_t launch_linear_fused(const uint16_t* x, const uint8_t* Wq, const uint16_t* sw, int64_t M, int64_t N, int64_t K,
                                int64_t G, uint16_t* Y, uint8_t* Aq, uint16_t* sa, hipStream_t stream, Dump dump,
                                bool wt) {
     if (!fused_linear_fits(M, N, K, G, wt)) return hipErrorInvalidValue;
+    if (wt) return launch_rows_fused(x, Wq, sw, N, K, G, Y, Aq, sa, stream, dump);
     const uint8_t* no_aq = nullptr;
     const uint16_t* no_sa = nullptr;
     switch (G) {
-        case 32: return launch_gemv_t<true, 4>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, wt, stream);
-        case 64: return launch_gemv_t<true, 8>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, wt, stream);
-        case 128: return launch_gemv_t<true, 16>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, wt, stream);
-        case 256: return launch_gemv_t<true, 32>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, wt, stream);
-        default: return launch_gemv_t<true, 64>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, wt, stream);
+        case 32: return launch_gemv_t<true, 4>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, stream);
+        case 64: return launch_gemv_t<true, 8>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, stream);
+        case 128: return launch_gemv_t<true, 16>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, stream);
+        case 256: return launch_gemv_t<true, 32>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, stream);
+        default: return launch_gemv_t<true, 64>(no_aq, no_sa, Wq, sw, N, K, G, Y, x, Aq, sa, dump, stream);
     }
 }
 

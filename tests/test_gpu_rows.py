@@ -1,0 +1,97 @@
+"""The few-row kernel (fewer than 256 rows at G >= 128 or per channel): its forms
+of 16, 32 and 64 rows by 32 or 64 columns, at the edges of their rows and
+columns, with fewer stages than waves, with scale rows of every alignment
+(K/G a multiple of 8 or not), sub-group partials and a partial last stage per
+channel.
+
+  * Y within the tolerance of the oracle in full, the same bits on both weight
+    layouts, through the workspace entry point when it picks the same kernel,
+    and from the debug form;
+  * the exact group sums of a row window against the oracle;
+  * one row with the quantizer in the prologue (tiled weights): Y and the work
+    buffers equal the quantizer followed by the GEMM, bit for bit.
+"""
+import numpy as np
+import pytest
+
+from parity import check_tolerance, dev, host, log
+from paper_2606_08761_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def pk():
+    import paper_2606_08761_amd as m
+    return m
+
+
+# (M, N, K, G): each form at its first and last row count (16 / 17, 32 / 33,
+# 64 / 65, 255); one column, one past a tile, an odd count of 32-column tiles;
+# one stage (seven idle waves), 9 stages, 26 and 27 groups (not a multiple of
+# 8); more column tiles than eight XCDs take evenly; G = 256, 512, 1024; per
+# channel with whole and partial last stages
+SHAPES = [(1, 33, 128, 128), (15, 1, 1152, 128), (16, 1000, 3328, 128), (17, 65, 1024, 128), (31, 8200, 256, 128),
+          (32, 8224, 1152, 128), (33, 1000, 3328, 128), (64, 520, 128, 128), (65, 2080, 1024, 128), (96, 16500, 256, 128),
+          (129, 4100, 640, 128), (255, 1056, 3456, 128), (200, 8200, 512, 128),
+          (16, 96, 2048, 256), (48, 1000, 2048, 512), (130, 520, 3072, 1024),
+          (9, 100, 96, 96), (16, 520, 4000, 4000), (32, 1000, 8192, 8192), (40, 65, 4000, 4000), (250, 2000, 1120, 1120)]
+
+
+@pytest.mark.parametrize("M,N,K,G", SHAPES)
+def test_rows(O, M, N, K, G):
+    import torch
+    m = pk()
+    plan, plan_ws = (m.apex4_w4a4_gemm_plan(e, M, N, K, G) for e in ("gemm", "gemm_ws"))
+    log(f"rows M={M} N={N} K={K} G={G}: {plan}, with a workspace {plan_ws}")
+    r = np.random.default_rng(M * 31 + N * 7 + K + G)
+    Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
+    sa, sw = wl.random_scales(r, M, K // G), wl.random_scales(r, N, K // G)
+    d = [dev(a) for a in (Aq, sa, Wq, sw)]
+    need = m.apex4_w4a4_gemm_workspace_size(M, N, K, G)
+    ws = torch.empty((max(need, 16),), dtype=torch.uint8, device="cuda")
+    Y = m.apex4_w4a4_gemm(*d, G)
+    Yw = m.apex4_w4a4_gemm_ws(*d, G, ws)
+    m0, mr = M // 3, min(7, M - M // 3)
+    Yd, P = m.apex4_w4a4_gemm_debug(*d, G, m0, mr)
+    P2 = m.apex4_w4a4_gemm_groupsums(d[0], d[2], G, m0, mr)
+    out = [Yd]
+    if G >= 128 and M > 1:  # one row: the dot-product kernel on row-major weights
+        Wt = m.apex4_tile_weights(d[2])
+        out.append(m.apex4_w4a4_gemm_tiled(d[0], d[1], Wt, d[3], G))
+        out.append(m.apex4_w4a4_gemm_debug(d[0], d[1], Wt, d[3], G, m0, mr, flags=m.APEX4_DEBUG_W_TILED)[0])
+    elif G >= 128:
+        check_tolerance(host(m.apex4_w4a4_gemm_tiled(d[0], d[1], m.apex4_tile_weights(d[2]), d[3], G)),
+                        O.gemm_rows(Aq, sa, Wq, sw, K, G), f"rows tiled {M}x{N}x{K} G{G}")
+    if plan_ws[0] == plan[0]:
+        out.append(Yw)
+    torch.cuda.synchronize()
+    assert all(torch.equal(y, Y) for y in out)
+    P_o = O.groupsums(Aq, Wq, K, G, m0, mr)
+    assert np.array_equal(host(P), P_o) and np.array_equal(host(P2), P_o)
+    y = O.gemm_rows(Aq, sa, Wq, sw, K, G)
+    check_tolerance(host(Y), y, f"rows {M}x{N}x{K} G{G}")
+    check_tolerance(host(Yw), y, f"rows with a workspace {M}x{N}x{K} G{G}")
+
+
+@pytest.mark.parametrize("N,K,G", [(1, 256, 128), (33, 3328, 128), (1000, 5120, 256), (9000, 4096, 512), (64, 40960, 128)])
+def test_rows_fused_one_row(O, N, K, G):
+    import torch
+    m = pk()
+    T = m.APEX4_DEBUG_W_TILED
+    assert m.apex4_w4a4_gemm_plan("linear", 1, N, K, G, T) == ("fused", 1)
+    x, w = wl.activations(wl.rng_for("decode", 61, N + K), 1, K), wl.weights(wl.rng_for("decode", 62, N + K), N, K)
+    Wq, sw = m.apex4_quantize_act(dev(w), G)
+    Wt = m.apex4_tile_weights(Wq)
+    Aq, sa = m.apex4_quantize_act(dev(x), G)
+    Aw = torch.full_like(Aq, 0xAB)
+    sw_ = torch.full_like(sa, float("nan"))
+    Y = m.apex4_w4a4_linear_tiled(dev(x), Wt, sw, G, A_q_work=Aw, s_a_work=sw_)
+    Yg = m.apex4_w4a4_gemm_tiled(Aq, sa, Wt, sw, G)
+    Yd, _, _, P = m.apex4_w4a4_linear_debug(dev(x), Wt, sw, G, flags=T)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Yg) and torch.equal(Yd, Y)
+    assert torch.equal(Aw, Aq) and torch.equal(sw_.view(torch.int16), sa.view(torch.int16))
+    Aq_o, sa_o = O.quantize(x, G)
+    Wq_o, sw_o = O.quantize(w, G)
+    assert np.array_equal(host(P), O.groupsums(Aq_o, Wq_o, K, G))
+    check_tolerance(host(Y), O.gemm_rows(Aq_o, sa_o, Wq_o, sw_o, K, G), f"rows fused N={N} K={K} G={G}")
