@@ -137,9 +137,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     const int n = (nks + NW - 1) / NW;  // stages per wave (the last may be past K)
 
     // ---- scales: 16-byte vectors of eight groups of a row where K/G is a
-    // multiple of 8, consecutive lanes on consecutive rows (the 2-byte LDS
-    // stores of a wave then land side by side); two vectors per thread are
-    // loaded before the ring, the rest (long K) after it
+    // multiple of 8, else pairs where it is even (rows are 4-byte aligned then),
+    // else one by one; consecutive lanes on consecutive rows (the 2-byte LDS
+    // stores of a wave then land side by side).  Two vectors or eight pairs per
+    // thread are loaded before the ring (behind it they would wait for it), the
+    // rest (long K) after it.
     const int nv = ng >> 3;
     const int nvec = ((ng & 7) == 0 && have_sc) ? ((FUSE ? 0 : ROWS) + COLS) * nv : 0;
     struct Slot {
@@ -170,7 +172,36 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
             for (int e = 0; e < 8; ++e) d[e * stride] = static_cast<uint16_t>(v[e >> 1] >> (16 * (e & 1)));
         }
     };
-    const v4u sv0 = sc_load(tid), sv1 = sc_load(tid + THREADS);
+    constexpr int A_LINES = FUSE ? 0 : ROWS, LINES = A_LINES + COLS, SU = 8;
+    const int npair = ((ng & 7) != 0 && (ng & 1) == 0 && have_sc) ? LINES * (ng >> 1) : 0;
+    uint32_t sv[SU];
+    auto pair_load = [&](int b0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < SU; ++u) {
+            if (b0 + u * THREADS >= npair) continue;  // uniform
+            const int i = min(b0 + tid + u * THREADS, npair - 1), c = i / LINES, r = i % LINES;
+            sv[u] = *reinterpret_cast<const uint32_t*>((r < A_LINES ? sa + static_cast<int64_t>(min(m0 + r, M - 1)) * ng
+                                                                    : sw + static_cast<int64_t>(min(n0 + r - A_LINES, N - 1)) * ng) + 2 * c);
+        }
+    };
+    auto pair_store = [&](int b0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < SU; ++u) {
+            if (b0 + u * THREADS >= npair) continue;
+            const int i = min(b0 + tid + u * THREADS, npair - 1), c = i / LINES, r = i % LINES;
+            const int stride = r < A_LINES ? ROWS : COLS;
+            uint16_t* d = (r < A_LINES ? asc + r : wsc + r - A_LINES) + 2 * c * stride;
+            d[0] = static_cast<uint16_t>(sv[u]);
+            d[stride] = static_cast<uint16_t>(sv[u] >> 16);
+        }
+    };
+    if (nvec > 0) {
+        const v4u a = sc_load(tid), b = sc_load(tid + THREADS);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sv[e] = a[e], sv[4 + e] = b[e];
+    } else if (npair > 0) {
+        pair_load(0);
+    }
 
     // ---- ring of PF stages; offsets within 32 bits (operands below 4 GiB)
     const uint32_t wbytes = wt ? static_cast<uint32_t>((N + 31) / 32) * static_cast<uint32_t>(nks) * 2048u
@@ -254,25 +285,21 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
             }
         }
     }
-    sc_store(tid, sv0);
-    sc_store(tid + THREADS, sv1);
-    for (int i = tid + 2 * THREADS; i < nvec; i += THREADS) sc_store(i, sc_load(i));
-    if ((ng & 7) != 0 && have_sc) {
-        // any other K/G: one scale at a time, eight loads in flight per thread
-        constexpr int A_LINES = FUSE ? 0 : ROWS, LINES = A_LINES + COLS, U = 8;
-        for (int i0 = tid; i0 < LINES * ng; i0 += U * THREADS) {
-            uint16_t v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = min(i0 + u * THREADS, LINES * ng - 1), g = i / LINES, r = i % LINES;
-                v[u] = r < A_LINES ? sa[static_cast<int64_t>(min(m0 + r, M - 1)) * ng + g]
-                                   : sw[static_cast<int64_t>(min(n0 + r - A_LINES, N - 1)) * ng + g];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = min(i0 + u * THREADS, LINES * ng - 1), g = i / LINES, r = i % LINES;
-                (r < A_LINES ? asc + g * ROWS + r : wsc + g * COLS + r - A_LINES)[0] = v[u];
-            }
+    if (nvec > 0) {
+        sc_store(tid, v4u{sv[0], sv[1], sv[2], sv[3]});
+        sc_store(tid + THREADS, v4u{sv[4], sv[5], sv[6], sv[7]});
+        for (int i = tid + 2 * THREADS; i < nvec; i += THREADS) sc_store(i, sc_load(i));
+    } else if (npair > 0) {
+        pair_store(0);
+        for (int b0 = SU * THREADS; b0 < npair; b0 += SU * THREADS) {
+            pair_load(b0);
+            pair_store(b0);
+        }
+    } else if (have_sc) {
+        for (int i = tid; i < LINES * ng; i += THREADS) {
+            const int g = i / LINES, r = i % LINES;
+            if (r < A_LINES) asc[g * ROWS + r] = sa[static_cast<int64_t>(min(m0 + r, M - 1)) * ng + g];
+            else wsc[g * COLS + r - A_LINES] = sw[static_cast<int64_t>(min(n0 + r - A_LINES, N - 1)) * ng + g];
         }
     }
     // accumulators: binary32, or the int32 sums per channel
