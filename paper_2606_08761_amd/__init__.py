@@ -98,29 +98,43 @@ def _check(fn: str, rc: int):
         raise Apex4Error(fn, rc, lib().apex4_status_string(rc).decode())
 
 
+# Small calls are bound by this marshalling (a launch takes the host about 4 us,
+# the binding took 10 more): torch is looked up once, pointers go to ctypes as
+# plain integers (every argument has its argtype), and the current stream's
+# handle is read without making a Stream object (0.1 us against 2 us).
+_torch_module = None
+_raw_stream = None
+
+
+def _torch():
+    global _torch_module, _raw_stream
+    if _torch_module is None:
+        import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+        _torch_module = torch
+    return _torch_module
+
+
 def _stream(t, stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(t.device)
-    return ctypes.c_void_p(stream.cuda_stream)
+    return _raw_stream(t.get_device()) if stream is None else stream.cuda_stream
 
 
 def _dev(t, dtype, name):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _torch().Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def apex4_quantize_act(x, G: int, A_q=None, s_a=None, stream=None):
     """SymQuant (b=4) of a [M, K] float16 tensor in groups of G along K.
 
     Returns (A_q uint8 [M, K/2], s_a float16 [M, K/G])."""
-    import torch
+    torch = _torch()
     M, K = x.shape
     if A_q is None:
         A_q = torch.empty((M, K // 2), dtype=torch.uint8, device=x.device)
@@ -134,7 +148,7 @@ def apex4_quantize_act(x, G: int, A_q=None, s_a=None, stream=None):
 
 def apex4_w4a4_gemm(A_q, s_a, W_q, s_w, G: int, Y=None, stream=None):
     """Y[M, N] = sum_g s_a[:, g] s_w[:, g]^T (.) (A_q,g W_q,g^T), float16 output."""
-    import torch
+    torch = _torch()
     M, K2 = A_q.shape
     N = W_q.shape[0]
     if Y is None:
@@ -157,7 +171,7 @@ def apex4_w4a4_gemm_ws(A_q, s_a, W_q, s_w, G: int, workspace=None, Y=None, strea
     """apex4_w4a4_gemm split over K when its tiles leave CUs idle; workspace is a
     uint8 device tensor of at least apex4_w4a4_gemm_workspace_size bytes (made
     here when None)."""
-    import torch
+    torch = _torch()
     M, K2 = A_q.shape
     N, K = W_q.shape[0], 2 * K2
     if Y is None:
@@ -176,7 +190,7 @@ def apex4_w4a4_gemm_ws(A_q, s_a, W_q, s_w, G: int, workspace=None, Y=None, strea
 def apex4_w4a4_gemm_noalloc(A_q, s_a, W_q, s_w, G: int, Y=None, stream=None):
     """apex4_w4a4_gemm_ws with the library's static per-device scratch in place
     of a workspace: the C call allocates nothing (Y is made here when None)."""
-    import torch
+    torch = _torch()
     M, K2 = A_q.shape
     N = W_q.shape[0]
     if Y is None:
@@ -190,7 +204,7 @@ def apex4_w4a4_gemm_noalloc(A_q, s_a, W_q, s_w, G: int, Y=None, stream=None):
 
 def apex4_w4a4_gemm_groupsums(A_q, W_q, G: int, m0: int = 0, mr: int | None = None, P=None, stream=None):
     """Exact int32 group sums P[i, n, g] for rows m0 .. m0+mr-1 (debug dump)."""
-    import torch
+    torch = _torch()
     M, K2 = A_q.shape
     N, K = W_q.shape[0], 2 * K2
     if mr is None:
@@ -205,7 +219,7 @@ def apex4_w4a4_gemm_groupsums(A_q, W_q, G: int, m0: int = 0, mr: int | None = No
 
 
 def _window(M, N, K, G, m0, mr, P, device):
-    import torch
+    torch = _torch()
     if mr is None:
         mr = M - m0
     if P is None:
@@ -219,7 +233,7 @@ def apex4_w4a4_gemm_debug(A_q, s_a, W_q, s_w, G: int, m0: int = 0, mr: int | Non
     uint8 device tensor) and, from the same launches, the exact int32 group
     sums P[i, n, g] of rows m0 .. m0+mr-1.  Returns (Y, P).  With
     flags & APEX4_DEBUG_W_TILED, W_q is tiled (N from s_w)."""
-    import torch
+    torch = _torch()
     M, K2 = A_q.shape
     N, K = s_w.shape[0], 2 * K2
     mr, P = _window(M, N, K, G, m0, mr, P, A_q.device)
@@ -237,7 +251,7 @@ def apex4_w4a4_gemm_debug(A_q, s_a, W_q, s_w, G: int, m0: int = 0, mr: int | Non
 
 def apex4_w4a4_linear(x, W_q, s_w, G: int, Y=None, A_q_work=None, s_a_work=None, stream=None):
     """Quantize x (SymQuant) then the W4A4 GEMM, both enqueued on one stream."""
-    import torch
+    torch = _torch()
     M, K = x.shape
     N = W_q.shape[0]
     if Y is None:
@@ -268,7 +282,7 @@ def apex4_w4a4_linear_debug(x, W_q, s_w, G: int, m0: int = 0, mr: int | None = N
     """apex4_w4a4_linear (or, with flags=APEX4_DEBUG_W_TILED, apex4_w4a4_linear_tiled)
     plus the exact int32 group sums of rows m0 .. m0+mr-1 from the same
     kernels.  Returns (Y, A_q_work, s_a_work, P)."""
-    import torch
+    torch = _torch()
     M, K = x.shape
     N = s_w.shape[0]
     mr, P = _window(M, N, K, G, m0, mr, P, x.device)
@@ -296,7 +310,7 @@ def apex4_tiled_weights_size(N: int, K: int) -> int:
 def apex4_tile_weights(W_q, W_t=None, stream=None):
     """Packed weight codes uint8 [N, K/2] -> the tiled layout, a flat uint8 tensor
     (offline, once per weight matrix)."""
-    import torch
+    torch = _torch()
     N, K2 = W_q.shape
     if W_t is None:
         W_t = torch.empty((apex4_tiled_weights_size(N, 2 * K2),), dtype=torch.uint8, device=W_q.device)
@@ -309,7 +323,7 @@ def apex4_tile_weights(W_q, W_t=None, stream=None):
 def apex4_w4a4_gemm_tiled(A_q, s_a, W_t, s_w, G: int, workspace=None, Y=None, stream=None):
     """apex4_w4a4_gemm on tiled weights (N from s_w); with a workspace tensor, the
     apex4_w4a4_gemm_ws kernel choice (split over K where it applies)."""
-    import torch
+    torch = _torch()
     M, K2 = A_q.shape
     N = s_w.shape[0]
     if Y is None:
@@ -325,7 +339,7 @@ def apex4_w4a4_gemm_tiled(A_q, s_a, W_t, s_w, G: int, workspace=None, Y=None, st
 
 def apex4_w4a4_linear_tiled(x, W_t, s_w, G: int, Y=None, A_q_work=None, s_a_work=None, stream=None):
     """apex4_w4a4_linear on tiled weights (N from s_w)."""
-    import torch
+    torch = _torch()
     M, K = x.shape
     N = s_w.shape[0]
     if Y is None:
@@ -350,7 +364,7 @@ def apex4_w4a4_linear_ws(x, W, s_w, G: int, workspace=None, tiled: bool = False,
     apex4_w4a4_gemm_workspace_size bytes.  When it is None: with
     make_workspace, one is made here if the shape needs one; without, none is
     passed (for callers that know the shape needs none).  N from s_w."""
-    import torch
+    torch = _torch()
     M, K = x.shape
     N = s_w.shape[0]
     if Y is None:
@@ -375,7 +389,7 @@ def apex4_w4a4_linear_ws(x, W, s_w, G: int, workspace=None, tiled: bool = False,
 
 def apex4_pack_fp6(q4, q6=None, stream=None):
     """Packed 4-bit codes uint8 [rows, K/2] -> FP6 e3m2 codes uint8 [rows, 3K/4]."""
-    import torch
+    torch = _torch()
     rows, K2 = q4.shape
     K = 2 * K2
     if q6 is None:
@@ -387,7 +401,7 @@ def apex4_pack_fp6(q4, q6=None, stream=None):
 
 def apex4_w4a4_gemm_fp6(A_6, s_a, W_6, s_w, G: int, Y=None, stream=None):
     """apex4_w4a4_gemm on FP6 containers (A_6 [M, 3K/4], W_6 [N, 3K/4]); G = 128."""
-    import torch
+    torch = _torch()
     M, K34 = A_6.shape
     N = W_6.shape[0]
     if Y is None:
@@ -401,7 +415,7 @@ def apex4_w4a4_gemm_fp6(A_6, s_a, W_6, s_w, G: int, Y=None, stream=None):
 
 def apex4_quantize_mx(x, G: int, Q6=None, e=None, stream=None):
     """MX variant quantizer: x [M, K] float16 -> (FP6 codes uint8 [M, 3K/4], E8M0 scales uint8 [M, K/G])."""
-    import torch
+    torch = _torch()
     M, K = x.shape
     if Q6 is None:
         Q6 = torch.empty((M, 3 * K // 4), dtype=torch.uint8, device=x.device)
@@ -415,7 +429,7 @@ def apex4_quantize_mx(x, G: int, Q6=None, e=None, stream=None):
 
 def apex4_w4a4_gemm_mx(A_6, e_a, W_6, e_w, G: int, Y=None, stream=None):
     """MX variant GEMM: power-of-two group scales applied inside the FP6 MFMA."""
-    import torch
+    torch = _torch()
     M, K34 = A_6.shape
     N = W_6.shape[0]
     if Y is None:
@@ -436,7 +450,7 @@ def apex4_w4a4_gemm_mx_workspace_size(M: int, N: int, K: int, G: int) -> int:
 
 def apex4_w4a4_gemm_mx_ws(A_6, e_a, W_6, e_w, G: int, workspace=None, Y=None, stream=None):
     """apex4_w4a4_gemm_mx split over K when its tiles leave CUs idle (workspace made here when None)."""
-    import torch
+    torch = _torch()
     M, K34 = A_6.shape
     N, K = W_6.shape[0], 4 * K34 // 3
     if Y is None:
@@ -483,7 +497,7 @@ class W4A4Linear:
     MAX_CACHED = 8
 
     def __init__(self, weight, G: int = 128, scales: str = "fp16", layout: str = "auto"):
-        import torch
+        torch = _torch()
         if weight.dim() != 2:
             raise ValueError("weight must be [N, K]")
         if scales not in ("fp16", "mx"):
@@ -502,12 +516,13 @@ class W4A4Linear:
         self.W_q, self.W_t = (None, apex4_tile_weights(W_q)) if self.tiled else (W_q, None)
         del W_q
         self._work = {}
+        self._recent = None
         self.device = weight.device
         self._torch = torch
 
-    def _buffers(self, M, stream):
-        key = (M, stream.cuda_stream)
-        buf = self._work.pop(key, None)
+    def _buffers(self, M, handle):
+        key = (M, handle)
+        buf = self._work.get(key)
         if buf is None:
             torch = self._torch
             size = apex4_w4a4_gemm_mx_workspace_size if self.mx else apex4_w4a4_gemm_workspace_size
@@ -518,29 +533,39 @@ class W4A4Linear:
                    torch.empty((M, max(self.K // self.G, 1)), dtype=sdt, device=self.device),
                    torch.empty((need,), dtype=torch.uint8, device=self.device) if need else None)
             while len(self._work) >= self.MAX_CACHED:
-                self._work.pop(next(iter(self._work)))
+                self._work.pop(next(iter(self._work)), None)
+        elif key == self._recent:
+            return buf
+        else:
+            self._work.pop(key, None)
         self._work[key] = buf  # most recently used last
+        self._recent = key
         return buf
 
     def __call__(self, x, stream=None):
-        lead = x.shape[:-1]
-        if x.shape[-1] != self.K:
-            raise ValueError(f"expected last dimension {self.K}, got {x.shape[-1]}")
-        x2 = x.reshape(-1, self.K).contiguous()
-        M = x2.shape[0]
-        if stream is None:
-            stream = self._torch.cuda.current_stream(x2.device)
-        Aq, sa, ws = self._buffers(M, stream)
+        torch = self._torch
+        shape = x.shape
+        if shape[-1] != self.K:
+            raise ValueError(f"expected last dimension {self.K}, got {shape[-1]}")
+        if not x.is_contiguous():
+            x = x.contiguous()
+        xp = _dev(x, torch.float16, "x")
+        M = x.numel() // self.K
+        handle = _stream(x, stream)
+        Aq, sa, ws = self._buffers(M, handle)
+        wsp, wsn = (None, 0) if ws is None else (ws.data_ptr(), ws.numel())
+        Y = x.new_empty((*shape[:-1], self.N))
+        L = lib()
         if self.mx:
-            apex4_quantize_mx(x2, self.G, Aq, sa, stream=stream)
-            if ws is None:
-                Y = apex4_w4a4_gemm_mx(Aq, sa, self.W_q, self.s_w, self.G, stream=stream)
-            else:
-                Y = apex4_w4a4_gemm_mx_ws(Aq, sa, self.W_q, self.s_w, self.G, ws, stream=stream)
+            Ap, ep, Wp, sp = Aq.data_ptr(), sa.data_ptr(), self.W_q.data_ptr(), self.s_w.data_ptr()
+            _check("apex4_quantize_mx", L.apex4_quantize_mx(xp, M, self.K, self.G, Ap, ep, handle))
+            _check("apex4_w4a4_gemm_mx_ws", L.apex4_w4a4_gemm_mx_ws(Ap, ep, Wp, sp, M, self.N, self.K, self.G,
+                                                                    Y.data_ptr(), wsp, wsn, handle))
         else:
             # one C call: the quantizer, then the GEMM (split over K or stream-K
             # where the cached workspace exists; fused for one row where it pays)
             W = self.W_t if self.tiled else self.W_q
-            Y = apex4_w4a4_linear_ws(x2, W, self.s_w, self.G, workspace=ws, tiled=self.tiled, A_q_work=Aq,
-                                     s_a_work=sa, stream=stream, make_workspace=False)
-        return Y.reshape(*lead, self.N)
+            _check("apex4_w4a4_linear_ws", L.apex4_w4a4_linear_ws(
+                xp, W.data_ptr(), self.s_w.data_ptr(), M, self.N, self.K, self.G, Y.data_ptr(), Aq.data_ptr(),
+                sa.data_ptr(), wsp, wsn, APEX4_DEBUG_W_TILED if self.tiled else 0, handle))
+        return Y
