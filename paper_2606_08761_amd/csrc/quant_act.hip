@@ -77,37 +77,60 @@ __global__ __launch_bounds__(256) void quant_small_kernel(const uint4* __restric
     }
 }
 
-// Large groups (G >= 1024, including per-channel G == K): one workgroup per
-// (row, group).  Pass 1 reduces amax over the group, pass 2 re-reads the
-// group (from cache) and writes the codes.
-__global__ __launch_bounds__(256) void quant_large_kernel(const uint4* __restrict__ x,
-                                                          int64_t slots_per_group,
-                                                          uint32_t* __restrict__ q,
-                                                          uint16_t* __restrict__ s) {
-    __shared__ uint32_t red[4];
+// Large groups (G >= 1024, including per-channel G == K): one workgroup of T
+// threads per (row, group), which it holds in registers, U slots per thread
+// (G <= 8 T U), so that x is read once, with all loads in flight together
+// (2 bytes read and 0.5 written per element; the two-pass form read x again
+// through the caches).
+// The rare slots with a quotient near a tie are redone at the end from a second
+// read: the call of pack8_ties then has no slots to keep across it.
+template <int T, int U>
+__global__ __launch_bounds__(T) void quant_large_kernel(const uint4* __restrict__ x, int slots_per_group,
+                                                        uint32_t* __restrict__ q, uint16_t* __restrict__ s) {
+    __shared__ uint32_t red[T / 64];
     const int64_t grp = blockIdx.x;
     const uint4* xg = x + grp * slots_per_group;
     uint32_t* qg = q + grp * slots_per_group;
+    uint4 v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const int i = static_cast<int>(threadIdx.x) + j * T;
+        v[j] = make_uint4(0u, 0u, 0u, 0u);
+        if (i < slots_per_group) {
+            const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xg) + i);
+            v[j] = make_uint4(t[0], t[1], t[2], t[3]);
+        }
+    }
     uint32_t am = 0;
-    for (int64_t i = threadIdx.x; i < slots_per_group; i += 256) {
-        const uint32_t a = absmax8_bits(xg[i]);
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const uint32_t a = absmax8_bits(v[j]);
         am = am > a ? am : a;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(am), off, 64));
-        am = am > o ? am : o;
-    }
+    am = group_max<64>(am);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = am;
     __syncthreads();
-    am = red[0] > red[1] ? red[0] : red[1];
-    am = am > red[2] ? am : red[2];
-    am = am > red[3] ? am : red[3];
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) am = am > red[w] ? am : red[w];
     uint16_t sbits;
     const float sf = scale_of(am, &sbits);
     const float inv = inv_of(sf);
-    for (int64_t i = threadIdx.x; i < slots_per_group; i += 256) qg[i] = pack8(xg[i], sf, inv);
+    uint32_t ties = 0;  // bit j: slot j
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const int i = static_cast<int>(threadIdx.x) + j * T;
+        if (i < slots_per_group) {
+            bool near_tie = false;
+            qg[i] = sf == 0.f ? 0u : pack8_fast(v[j], inv, &near_tie);
+            if (near_tie) ties |= 1u << j;
+        }
+    }
     if (threadIdx.x == 0) s[grp] = sbits;
+    if (sf == 0.f) return;
+    for (; ties; ties &= ties - 1) {
+        const int i = static_cast<int>(threadIdx.x) + (__ffs(static_cast<int>(ties)) - 1) * T;
+        qg[i] = pack8_ties(xg[i], sf, inv);
+    }
 }
 
 template <int L, int U>
@@ -130,6 +153,37 @@ hipError_t launch_small(const uint16_t* x, int64_t nslots, uint8_t* q, uint16_t*
     return launch_small_u<L, 1>(x, nslots, q, s, st);
 }
 
+template <int T, int U>
+hipError_t launch_large_tu(const uint16_t* x, int64_t groups, int64_t spg, uint8_t* q, uint16_t* s, hipStream_t st) {
+    hipLaunchKernelGGL((quant_large_kernel<T, U>), dim3(static_cast<unsigned>(groups)), dim3(T), 0, st,
+                       reinterpret_cast<const uint4*>(x), static_cast<int>(spg), reinterpret_cast<uint32_t*>(q), s);
+    return hipGetLastError();
+}
+
+// spg = G / 8 slots per group: any multiple of 4, since G == K may be any
+// multiple of 32.  One slot per thread up to 256, and up to 1024 where there are
+// fewer groups than CUs (all of a group's loads go out at once); more groups
+// than CUs fill the chip with smaller workgroups and several slots per thread.
+// Against reading the group twice (MI355X, us): 16 rows of 28672 10.4 -> 4.8,
+// 256 rows of 8192 5.1 -> 3.5, 2048 rows of 8192 13.2 -> 11.4 and of 28672
+// 44.3 -> 30.4, 4096 rows of 8192 in groups of 1024 31.5 -> 20.1.
+hipError_t launch_large(const uint16_t* x, int64_t groups, int64_t spg, uint8_t* q, uint16_t* s, hipStream_t st) {
+    if (spg <= 64) return launch_large_tu<64, 1>(x, groups, spg, q, s, st);
+    if (spg <= 128) return launch_large_tu<128, 1>(x, groups, spg, q, s, st);
+    if (spg <= 256) return launch_large_tu<256, 1>(x, groups, spg, q, s, st);
+    if (groups > device_cu_count()) {
+        if (spg <= 512) return launch_large_tu<256, 2>(x, groups, spg, q, s, st);
+        if (spg <= 1024) return launch_large_tu<256, 4>(x, groups, spg, q, s, st);
+        if (spg <= 2048) return launch_large_tu<512, 4>(x, groups, spg, q, s, st);
+    }
+    if (spg <= 512) return launch_large_tu<512, 1>(x, groups, spg, q, s, st);
+    if (spg <= 1024) return launch_large_tu<1024, 1>(x, groups, spg, q, s, st);
+    if (spg <= 2048) return launch_large_tu<1024, 2>(x, groups, spg, q, s, st);
+    if (spg <= 4096) return launch_large_tu<1024, 4>(x, groups, spg, q, s, st);
+    if (spg <= 8192) return launch_large_tu<1024, 8>(x, groups, spg, q, s, st);
+    return hipErrorInvalidValue;  // the entry points take rows of one group up to 65536
+}
+
 }  // namespace
 
 hipError_t launch_quantize(const uint16_t* x, int64_t M, int64_t K, int64_t G, uint8_t* q,
@@ -145,9 +199,7 @@ hipError_t launch_quantize(const uint16_t* x, int64_t M, int64_t K, int64_t G, u
     }
     const int64_t groups = M * (K / G);
     if (groups > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(quant_large_kernel, dim3(static_cast<unsigned>(groups)), dim3(256), 0, stream,
-                       reinterpret_cast<const uint4*>(x), G / 8, reinterpret_cast<uint32_t*>(q), s);
-    return hipGetLastError();
+    return launch_large(x, groups, G / 8, q, s, stream);
 }
 
 }  // namespace apex4

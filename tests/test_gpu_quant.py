@@ -138,3 +138,26 @@ def test_every_binary16_value(O, G):
     x = _every_value_groups(G, bits)
     log(f"quantize every binary16 value G={G} ({x.shape[0]} x {x.shape[1]})")
     assert_same(x, G, O, f"every value G={G}")
+
+
+@pytest.mark.parametrize("M", [2, 300])   # fewer and more groups than CUs
+@pytest.mark.parametrize("K", [32 * 3, 512 + 32, 1024 + 32, 2048, 2048 + 32, 4096, 4096 + 32, 8192 + 32,
+                               16384, 16384 + 32, 32768, 32768 + 32])
+def test_per_channel_register_sizes(O, M, K):
+    """One group per row at the edges of each workgroup form: the last thread's
+    slots, exact ties (redone from a second read), zero rows."""
+    log(f"quantize per channel M={M} K={K}")
+    r = wl.rng_for("gsweep", 7, K)
+    x = wl.activations(r, M, K)
+    x[0] = 0
+    x[1] = ((np.arange(K) % 15) - 7) * 0.5   # scale 0.5: whole quotients
+    x[1, ::3] = 1.25                         # quotient 2.5 exactly
+    x[1, -1] = 3.5
+    assert_same(x, K, O, f"per channel M={M} K={K}")
+
+
+def test_per_channel_longest(O):
+    K = 65536
+    log(f"quantize per channel M=2 K={K}")
+    x = wl.activations(wl.rng_for("gsweep", 7, K), 2, K)
+    assert_same(x, K, O, f"per channel M=2 K={K}")
