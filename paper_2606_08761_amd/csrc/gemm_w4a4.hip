@@ -1022,8 +1022,13 @@ hipError_t launch_k(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, co
     // Small tiles (one wave per SIMD) have little compute per stage to hide a
     // load behind: their loads run 4 stages ahead (measured 4-7 % faster at
     // M = 64..256, N = 8192 for G in {128, 256}, 24 % for G = K).  With G < 128
-    // the deeper ring costs occupancy and time, so those keep one stage.
-    constexpr int PF = (WAVES_M * WAVES_N * MI * NJ <= 8 && GPS == 1) ? 4 : 1;
+    // the deeper ring costs occupancy and time, so those keep one stage.  Of the
+    // 128 x 256 tiles those of G in {512, 1024} load 2 stages ahead (M = 2048,
+    // N = K = 8192: 152.4 -> 149.7 and 142.9 -> 141.0 us); per channel the
+    // second stage takes the registers of the second workgroup per CU (117 ->
+    // 121 us), at G in {32, 64} it lengthens the loop (351 -> 389, 240 -> 256).
+    constexpr bool small = WAVES_M * WAVES_N * MI * NJ <= 8;
+    constexpr int PF = small && GPS == 1 ? 4 : MODE == kPersist && !DUMP ? 2 : 1;
     const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(S)), block(64 * WAVES_M * WAVES_N * KSPLIT);
     const int m = static_cast<int>(M), n = static_cast<int>(N), k = static_cast<int>(K), g = static_cast<int>(G);
     const int nks = static_cast<int>(kstages(K) / S), w = wt ? 1 : 0;
