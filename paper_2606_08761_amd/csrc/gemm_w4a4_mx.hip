@@ -40,6 +40,8 @@ namespace {
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x32 __attribute__((ext_vector_type(32)));
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 
 constexpr int MX_SROW = 96;        // FP6 bytes of one row per 128-wide stage
 constexpr int MX_LROW = 112;       // padded LDS row (28 dwords)
@@ -84,17 +86,37 @@ __global__ __launch_bounds__(256) void quant_mx_kernel(const uint16_t* __restric
         const float f = frexpf(__half2float(__ushort_as_half(static_cast<uint16_t>(amax))), &k);
         E = f <= 0.875f ? k - 3 : k - 2;
     }
-    uint32_t out[6] = {0u, 0u, 0u, 0u, 0u, 0u};
+    uint32_t out[6];
+    if (amax < 0x7C00u) {
+        // finite group: |x| <= 7 * 2^E, so x 2^-E (exact in binary32: E in
+        // [-26, 14]) rounds, half to even, to a code of magnitude <= 7, exact in
+        // binary16 and in e3m2; one instruction packs the 32 of them.  The kernel
+        // was bound by its vector work, a table look-up and three shifts per code
+        // (2048 rows of 8192, G = 32: 10.9 -> 8.9 us; 4096, G = 128: 20.9 -> 15.1)
+        const float inv = __uint_as_float(static_cast<uint32_t>(127 - E) << 23);
+        f16x32 c;
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
-        const uint16_t bits = static_cast<uint16_t>(h[j >> 1] >> (16 * (j & 1)));
-        // x 2^-E is exact, rintf rounds half to even; |q| <= 7 by the choice of E
-        const float v = ldexpf(__half2float(__ushort_as_half(bits)), -E);
-        const int q = max(-8, min(7, static_cast<int>(rintf(v))));
-        const uint32_t c = e3m2_of(q);
-        const int bit = 6 * j;
-        out[bit >> 5] |= c << (bit & 31);
-        if ((bit & 31) > 26) out[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
+        for (int j = 0; j < 32; ++j) {
+            const uint16_t bits = static_cast<uint16_t>(h[j >> 1] >> (16 * (j & 1)));
+            c[j] = static_cast<_Float16>(rintf(__half2float(__ushort_as_half(bits)) * inv) + 0.0f);  // -0 + 0 = +0: zero has no sign bit
+        }
+        const u32x6 p = __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(c, 1.0f);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) out[i] = p[i];
+    } else {
+        // a group with an infinity or a NaN: clamped integers
+#pragma unroll
+        for (int i = 0; i < 6; ++i) out[i] = 0u;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const uint16_t bits = static_cast<uint16_t>(h[j >> 1] >> (16 * (j & 1)));
+            const float v = ldexpf(__half2float(__ushort_as_half(bits)), -E);
+            const int q = max(-8, min(7, static_cast<int>(rintf(v))));
+            const uint32_t c = e3m2_of(q);
+            const int bit = 6 * j;
+            out[bit >> 5] |= c << (bit & 31);
+            if ((bit & 31) > 26) out[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
+        }
     }
     uint2* dst = reinterpret_cast<uint2*>(q6 + row * (3 * static_cast<int64_t>(K) / 4) + 24 * blk);
     dst[0] = make_uint2(out[0], out[1]);

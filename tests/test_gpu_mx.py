@@ -60,6 +60,33 @@ def test_quantizer_edge_groups():
     assert np.array_equal(Q6, ofp6.pack_fp6(codes_o))
 
 
+@pytest.mark.parametrize("G", [32, 128, 1024])
+def test_quantizer_every_finite_value(G):
+    """Every finite binary16 pattern, in groups of one magnitude range (sorted)
+    and of mixed ones; negative values that round to zero carry no sign."""
+    bits = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    bits = bits[(bits & 0x7C00) != 0x7C00]
+    x = np.concatenate([bits, np.random.default_rng(5).permutation(bits)]).view(np.float16).reshape(-1, 1024)
+    Q6, e, codes_o, e_o = quantize_both(x, G)
+    assert np.array_equal(e, e_o)
+    assert np.array_equal(Q6, ofp6.pack_fp6(codes_o))
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_quantizer_non_finite_group_stays_alone(bad):
+    """An infinity or a NaN takes its own group through the clamped path; the
+    lanes beside it keep their codes."""
+    x = wl.activations(wl.rng_for("tiny", 51, 0), 4, 2048)
+    y = x.copy()
+    y[:, 64 + 5] = bad
+    Q6, e, codes_o, e_o = quantize_both(x, 32)
+    P6, f = (host(t) for t in pk().apex4_quantize_mx(dev(y), 32))
+    keep = np.arange(64) != 2
+    assert np.array_equal(f[:, keep], e_o[:, keep])
+    want = ofp6.pack_fp6(codes_o).reshape(4, 64, 24)
+    assert np.array_equal(P6.reshape(4, 64, 24)[:, keep], want[:, keep])
+
+
 def gemm_from_oracle_operands(Aq, ea, Wq, ew, G):
     m = pk()
     return host(m.apex4_w4a4_gemm_mx(dev(ofp6.pack_fp6(Aq)), dev(ea), dev(ofp6.pack_fp6(Wq)), dev(ew), G))
