@@ -77,9 +77,9 @@ __global__ __launch_bounds__(256) void quant_small_kernel(const uint4* __restric
     }
 }
 
-// Large groups (G >= 1024, including per-channel G == K): one workgroup of T
-// threads per (row, group), which it holds in registers, U slots per thread
-// (G <= 8 T U), so that x is read once, with all loads in flight together
+// Large groups (G >= 1024, including per-channel G == K) up to 65536: one
+// workgroup of T threads per (row, group), which it holds in registers, U slots
+// per thread (G <= 8 T U), so that x is read once, with all loads in flight together
 // (2 bytes read and 0.5 written per element; the two-pass form read x again
 // through the caches).
 // The rare slots with a quotient near a tie are redone at the end from a second
@@ -133,6 +133,31 @@ __global__ __launch_bounds__(T) void quant_large_kernel(const uint4* __restrict_
     }
 }
 
+// Groups too long for the registers of one workgroup (G > 65536): one workgroup
+// of 1024 threads per (row, group), x read twice, the second time for the codes.
+__global__ __launch_bounds__(1024) void quant_long_kernel(const uint4* __restrict__ x, int slots_per_group,
+                                                          uint32_t* __restrict__ q, uint16_t* __restrict__ s) {
+    __shared__ uint32_t red[16];
+    const int64_t grp = blockIdx.x;
+    const uint4* xg = x + grp * slots_per_group;
+    uint32_t* qg = q + grp * slots_per_group;
+    uint32_t am = 0;
+    for (int i = static_cast<int>(threadIdx.x); i < slots_per_group; i += 1024) {
+        const uint32_t a = absmax8_bits(xg[i]);
+        am = am > a ? am : a;
+    }
+    am = group_max<64>(am);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = am;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 16; ++w) am = am > red[w] ? am : red[w];
+    uint16_t sbits;
+    const float sf = scale_of(am, &sbits);
+    const float inv = inv_of(sf);
+    for (int i = static_cast<int>(threadIdx.x); i < slots_per_group; i += 1024) qg[i] = pack8(xg[i], sf, inv);
+    if (threadIdx.x == 0) s[grp] = sbits;
+}
+
 template <int L, int U>
 hipError_t launch_small_u(const uint16_t* x, int64_t nslots, uint8_t* q, uint16_t* s, hipStream_t st) {
     const int64_t blocks_needed = (nslots + 256 * U - 1) / (256 * U);
@@ -160,8 +185,8 @@ hipError_t launch_large_tu(const uint16_t* x, int64_t groups, int64_t spg, uint8
     return hipGetLastError();
 }
 
-// spg = G / 8 slots per group: any multiple of 4, since G == K may be any
-// multiple of 32.  One slot per thread up to 256, and up to 1024 where there are
+// spg = G / 8 slots per group: any multiple of 4, since G may be any multiple of
+// 32 that divides K, of any length.  One slot per thread up to 256, and up to 1024 where there are
 // fewer groups than CUs (all of a group's loads go out at once); more groups
 // than CUs fill the chip with smaller workgroups and several slots per thread.
 // Against reading the group twice (MI355X, us): 16 rows of 28672 10.4 -> 4.8,
@@ -181,7 +206,9 @@ hipError_t launch_large(const uint16_t* x, int64_t groups, int64_t spg, uint8_t*
     if (spg <= 2048) return launch_large_tu<1024, 2>(x, groups, spg, q, s, st);
     if (spg <= 4096) return launch_large_tu<1024, 4>(x, groups, spg, q, s, st);
     if (spg <= 8192) return launch_large_tu<1024, 8>(x, groups, spg, q, s, st);
-    return hipErrorInvalidValue;  // the entry points take rows of one group up to 65536
+    hipLaunchKernelGGL(quant_long_kernel, dim3(static_cast<unsigned>(groups)), dim3(1024), 0, st,
+                       reinterpret_cast<const uint4*>(x), static_cast<int>(spg), reinterpret_cast<uint32_t*>(q), s);
+    return hipGetLastError();
 }
 
 }  // namespace

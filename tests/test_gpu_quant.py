@@ -161,3 +161,16 @@ def test_per_channel_longest(O):
     log(f"quantize per channel M=2 K={K}")
     x = wl.activations(wl.rng_for("gsweep", 7, K), 2, K)
     assert_same(x, K, O, f"per channel M=2 K={K}")
+
+
+@pytest.mark.parametrize("K,G", [(65568, 65568), (131072, 131072), (262144, 131072), (3 * 65568, 65568)])
+def test_groups_past_the_registers(O, K, G):
+    """Any multiple of 32 that divides K is a group size, also past the 65536
+    values that a workgroup holds in registers."""
+    log(f"quantize M=3 K={K} G={G}")
+    x = wl.activations(wl.rng_for("gsweep", 7, K), 3, K)
+    x[1] = ((np.arange(K) % 15) - 7) * 0.5   # scale 0.5
+    x[1, ::3] = 1.25                         # quotient 2.5 exactly
+    x[1, -1] = 3.5
+    x[2, :G] = 0
+    assert_same(x, G, O, f"K={K} G={G}")
