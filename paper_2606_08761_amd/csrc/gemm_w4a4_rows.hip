@@ -328,15 +328,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     auto process = [&](auto J, int i) __attribute__((always_inline)) {
         constexpr int j = decltype(J)::value;
         const int s = wave + NW * i;
-        const bool live = s < nks;
-        const int g = min(s, nks - 1) >> lg;
+        const int g = s >> lg;
         // activation operands: b = row block (RB >= 1) of four MFMAs, or the one
         // 16-row operand of two
         constexpr int KM = RB == 0 ? 2 : 4;
         i32x4 af[RB == 0 ? 1 : RB][KM];
         if constexpr (RB == 0) {
             v4u a;
-            if constexpr (FUSE) a = *reinterpret_cast<const v4u*>(codes + min(s, nks - 1) * 64 + 16 * lq);
+            if constexpr (FUSE) a = *reinterpret_cast<const v4u*>(codes + s * 64 + 16 * lq);
             else a = ra[j][0];
             af[0][0] = rfrag(a[0], a[1]);
             af[0][1] = rfrag(a[2], a[3]);
@@ -371,7 +370,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
             float s1[RB == 0 ? 2 : 1];
 #pragma unroll
             for (int b = 0; b < (RB == 0 ? 2 : 1); ++b)
-                s1[b] = (!CH && have_sc && live) ? rh2f(wsc[g * COLS + 32 * c + col_of(b)]) * (1.0f / 256.0f) : 0.f;
+                s1[b] = (!CH && have_sc) ? rh2f(wsc[g * COLS + 32 * c + col_of(b)]) * (1.0f / 256.0f) : 0.f;
             Acc d[NB];
             if constexpr (RB == 0) {
                 uint32_t w[2][4];
@@ -411,7 +410,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
                     if constexpr (DUMP) {
                         int col = n0 + 32 * c + col_of(b);
                         asm volatile("" : "+v"(col));  // no address is kept from stage to stage (registers)
-                        if (live && col < N) {
+                        if (col < N) {
 #pragma unroll
                             for (int r = 0; r < AV; ++r) {
                                 const int row = m0 + row_of(b, r);
@@ -438,7 +437,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     for (int q0 = 0; q0 < n; q0 += PF)
         unroll<PF>([&](auto J) __attribute__((always_inline)) {
             constexpr int j = decltype(J)::value;
-            if (q0 + j < n) process(J, q0 + j);
+            if (wave + NW * (q0 + j) < nks) process(J, q0 + j);  // uniform: no stage past K (its scales are not there)
             __builtin_amdgcn_sched_barrier(0);  // the stage's registers are read before its slot is loaded again
             load(J, q0 + j + PF);
         });

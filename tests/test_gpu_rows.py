@@ -95,3 +95,41 @@ def test_rows_fused_one_row(O, N, K, G):
     Wq_o, sw_o = O.quantize(w, G)
     assert np.array_equal(host(P), O.groupsums(Aq_o, Wq_o, K, G))
     check_tolerance(host(Y), O.gemm_rows(Aq_o, sa_o, Wq_o, sw_o, K, G), f"rows fused N={N} K={K} G={G}")
+
+
+def formula(O, Aq, sa, Wq, sw, K, G):
+    """Y = sum_g s_a s_w P in binary64 with IEEE infinities and NaN."""
+    P = O.groupsums(Aq, Wq, K, G).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        return (sa.astype(np.float64)[:, None, :] * (sw.astype(np.float64)[None] * P)).sum(axis=2)
+
+
+# (M, N, K, G), K/128 not a multiple of the waves (past K they have no stage):
+# 16, 32 and 64 rows a workgroup, fewer stages than waves, per channel with a
+# partial last stage
+DEAD = [(1, 33, 1152, 128), (16, 100, 1152, 128), (20, 100, 384, 128), (40, 200, 1152, 128), (72, 8192, 1152, 128),
+        (16, 100, 1184, 1184), (40, 200, 1184, 1184)]
+
+
+@pytest.mark.parametrize("M,N,K,G", DEAD)
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_rows_non_finite_scale(O, M, N, K, G, value):
+    """A non-finite activation scale gives what the formula gives, and only in
+    its own row: no wave multiplies it with a weight scale that is not there."""
+    m = pk()
+    r = np.random.default_rng(M + N + K + G)
+    Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
+    sa, sw = wl.random_scales(r, M, K // G), wl.random_scales(r, N, K // G)
+    sa[M // 2, -1] = value   # the last group: the one that waves past K would read
+    log(f"rows scale {value} M={M} N={N} K={K} G={G}: {m.apex4_w4a4_gemm_plan('gemm', M, N, K, G)}")
+    d = [dev(a) for a in (Aq, sa, Wq, sw)]
+    outs = [m.apex4_w4a4_gemm_tiled(d[0], d[1], m.apex4_tile_weights(d[2]), d[3], G)]
+    if M > 1:  # one row on row-major weights is the dot-product kernel, which scales parts of a group
+        outs.append(m.apex4_w4a4_gemm(*d, G))
+    y = formula(O, Aq, sa, Wq, sw, K, G)
+    bad = np.arange(M) == M // 2
+    assert not np.isfinite(y[bad]).any()
+    for Y in outs:
+        Y = host(Y)
+        check_tolerance(Y[~bad], y[~bad]) if M > 1 else None
+        assert np.array_equal(Y[bad], y[bad].astype(np.float16), equal_nan=True)
