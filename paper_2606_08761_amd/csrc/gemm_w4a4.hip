@@ -1258,15 +1258,20 @@ namespace {
 // rows, split S ways over K (the planes' bytes are written and read): least
 // squares over 343 shapes of 40 .. 250 rows, N = 1024 .. 28672, K = 1024 ..
 // 28672 on MI355X, within 30 % of each.
-// Per channel: 190 shapes.
-double tile_cost_us(int64_t M, int64_t N, int64_t K, bool ch, int S) {
+// Per channel: 190 shapes.  Groups of several stages (G = 256, 512, 1024, one
+// dequantization per group): 415 shapes, N = 512 .. 57344, G in equal parts,
+// within 50 % of each.
+double tile_cost_us(int64_t M, int64_t N, int64_t K, int64_t G, int S) {
+    const bool ch = G == K, whole = G > 128 && !ch;
     const int64_t cus = device_cu_count();
     const double n = static_cast<double>(kstages(K));
     const double mbytes = 1e-6 * S * static_cast<double>(M * N * 4);
+    if (S > 1 && whole) return 5.6 + 0.605 * n / S + 0.98 * mbytes;
     if (S > 1) return ch ? 5.5 + 0.464 * n / S + 0.89 * mbytes : 8.4 + 1.08 * n / S + 0.36 * mbytes;
     const int64_t big = ((M + 127) / 128) * ((N + 255) / 256), small = ((M + 63) / 64) * ((N + 127) / 128);
     const double rounds = static_cast<double>(((big >= cus ? big : small) + cus - 1) / cus);
-    if (big >= cus) return 4.0 + (ch ? 0.9 : 1.25) * n * rounds;
+    if (big >= cus) return whole ? 8.9 + 1.1 * n * rounds : 4.0 + (ch ? 0.9 : 1.25) * n * rounds;
+    if (whole) return rounds == 1.0 ? 4.6 + 0.401 * n : 0.5 + rounds * (2.56 + 0.368 * n);
     if (ch) return rounds == 1.0 ? 5.1 + 0.27 * n : 3.2 + rounds * (1.3 + 0.262 * n);
     return rounds == 1.0 ? 4.7 + 0.4 * n : 1.5 + rounds * (1.8 + 0.429 * n);
 }
@@ -1276,9 +1281,14 @@ double tile_cost_us(int64_t M, int64_t N, int64_t K, bool ch, int S) {
 // tile kernels on average, choosing by these costs loses 0.4 % against the
 // faster of the two (64 rows, N = K = 8192: 14 against 23 us split over K;
 // N = 57344: 69 against 76; 128 rows: 20 against 29; but 250 rows, N = 28672,
-// K = 1024: 28 against 22 on 64 x 128 tiles).
+// K = 1024: 28 against 22 on 64 x 128 tiles).  Groups of several stages, which
+// both kernels dequantize once: over their 415 shapes the choice loses 0.6 %
+// (at most 18 %), and the few-row kernel is 1.3 to 1.4 times as fast as the tile
+// kernels with a workspace, 1.5 to 1.8 times without (64 rows, N = 28672,
+// K = 8192, G = 256: 40 against 38 us; 200 rows, N = 28672, K = 2048: 34 against
+// 32; 64 rows, N = 3072, K = 20480, G = 512: 26.5 against 22.6 split over K).
 bool rows_take(int64_t M, int64_t N, int64_t K, int64_t G, int S) {
-    return rows_fits(M, N, K, G) && (M <= 32 || rows_cost_us(M, N, K, G) < tile_cost_us(M, N, K, G == K, S));
+    return rows_fits(M, N, K, G) && (M <= 32 || rows_cost_us(M, N, K, G) < tile_cost_us(M, N, K, G, S));
 }
 
 }  // namespace

@@ -36,7 +36,13 @@
 //   * Dequantization per stage as in the other kernels: the accumulator starts
 //     from 1.5 * 2^23, so the group (or 128-wide partial) sum reads as binary32,
 //     t = fma(D, s_w / 256, -1.5 * 2^23 s_w / 256), acc = fma(t, s_a, acc).
-//     Splitting a group into 128-wide partials changes only the fp32 rounding.
+//     Up to 32 rows a group of several stages is split into 128-wide partials,
+//     as in the persistent few-row kernel: that changes only the fp32 rounding.
+//   * Past 32 rows (kWhole) a wave takes all stages of a group, one after the
+//     other, and the int32 sum meets the scales once, as in the tile kernels
+//     (binary32 partials of a group that cancel would leave 2^-24 of the
+//     partials, not of their sum).  The waves then share the groups, not the
+//     stages: uneven where K/G is not a multiple of the waves.
 //   * Per channel (CH): the int32 sums run over all of the wave's stages, the
 //     waves' sums are added exactly and scaled once (the same bits as the tile
 //     kernels); K % 128 != 0 only occurs here, and pieces past the row's end
@@ -103,7 +109,11 @@ struct Form {
     static constexpr int64_t scale_bytes(int64_t ng) { return ((ROWS + COLS) * ng * 2 + 15) / 16 * 16; }
 };
 
-template <int RB, int CT, int NW, int PF, int OCC, bool NT, bool CH, bool DUMP, int QL>
+// What meets the scales: a stage's sum (up to 32 rows, and G = 128), a whole
+// group's (several stages, one after the other in one wave), or the row's.
+enum RowsMode : int { kStage, kWhole, kChan };
+
+template <int RB, int CT, int NW, int PF, int OCC, bool NT, int MODE, bool DUMP, int QL>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     const uint8_t* __restrict__ Aq, const uint16_t* __restrict__ sa, const uint8_t* __restrict__ Wq,
     const uint16_t* __restrict__ sw, int M, int N, int K, int lg, int ng, uint16_t* __restrict__ Y, int wt,
@@ -113,8 +123,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     constexpr int ROWS = F::ROWS, COLS = F::COLS, NRT = F::NRT, NR = F::NR;
     constexpr int THREADS = 64 * NW;
     constexpr int NA = RB == 0 ? 1 : 2 * RB;  // 16-byte activation loads per stage
-    constexpr bool FUSE = QL > 0;
-    static_assert(!FUSE || (RB == 0 && !CH), "the fused prologue quantizes one row");
+    constexpr bool FUSE = QL > 0, CH = MODE == kChan, WHOLE = MODE == kWhole;
+    static_assert(!FUSE || (RB == 0 && MODE == kStage), "the fused prologue quantizes one row");
     const bool have_sc = FUSE || !DUMP || sa != nullptr;  // uniform
     // scales group-major ([ng][ROWS], then [ng][COLS]), then (FUSE) the row's
     // codes; the reduction reuses the place, past the scales per channel
@@ -134,7 +144,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     const int ct = (bj / rblocks) * 8 + static_cast<int>(blockIdx.x & 7);
     const int n0 = ct * COLS, m0 = (bj % rblocks) * ROWS;
     if (n0 >= N) return;  // the last eight tiles' spare workgroups
-    const int n = (nks + NW - 1) / NW;  // stages per wave (the last may be past K)
+    // a wave's i-th stage, and the stages per wave (the last may be past K)
+    auto stage_of = [&](int i) __attribute__((always_inline)) {
+        return WHOLE ? ((i >> lg) * NW + wave) << lg | (i & ((1 << lg) - 1)) : wave + NW * i;
+    };
+    const int n = WHOLE ? (ng + NW - 1) / NW << lg : (nks + NW - 1) / NW;
 
     // ---- scales: 16-byte vectors of eight groups of a row where K/G is a
     // multiple of 8, else pairs where it is even (rows are 4-byte aligned then),
@@ -226,7 +240,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     v4u rw[PF][2 * CT], ra[PF][NA];
     auto load = [&](auto J, int i) __attribute__((always_inline)) {
         constexpr int j = decltype(J)::value;
-        const int s = wave + NW * i;
+        const int s = stage_of(i);
         const bool live = s < nks;  // uniform: a stage past K loads from an empty range
         const auto wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(Wq), 0, live ? wbytes : 0u, RSRC_FLAGS);
         const int ws = live ? s * w_ss : 0, as = live ? s * 64 : 0;
@@ -302,20 +316,22 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
             else wsc[g * COLS + r - A_LINES] = sw[static_cast<int64_t>(min(n0 + r - A_LINES, N - 1)) * ng + g];
         }
     }
-    // accumulators: binary32, or the int32 sums per channel
+    // accumulators: binary32, the int32 sums of the group in progress or of the row
     using Acc = std::conditional_t<RB == 0, i32x4, i32x16>;
     constexpr int AV = RB == 0 ? 4 : 16;
     constexpr int NB = RB == 0 ? 2 : RB;  // MFMA results per column tile: column halves, or row blocks
     float acc[CH ? 1 : CT][CH ? 1 : NRT];
-    Acc isum[CH ? CT : 1][CH ? NB : 1];
-    if constexpr (CH) {
+    constexpr bool INT = CH || WHOLE;
+    Acc isum[INT ? CT : 1][INT ? NB : 1];
+    if constexpr (INT) {
 #pragma unroll
         for (int c = 0; c < CT; ++c)
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int r = 0; r < AV; ++r) isum[c][b][r] = 0;
-    } else {
+    }
+    if constexpr (!CH) {
 #pragma unroll
         for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -327,8 +343,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     auto col_of = [&](int b) { return RB == 0 ? 16 * b + l16 : l32; };
     auto process = [&](auto J, int i) __attribute__((always_inline)) {
         constexpr int j = decltype(J)::value;
-        const int s = wave + NW * i;
-        const int g = s >> lg;
+        const int s = stage_of(i), g = s >> lg;
+        const bool deq = !CH && have_sc && (!WHOLE || ((i + 1) & ((1 << lg) - 1)) == 0);  // uniform
         // activation operands: b = row block (RB >= 1) of four MFMAs, or the one
         // 16-row operand of two
         constexpr int KM = RB == 0 ? 2 : 4;
@@ -354,7 +370,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
             }
         }
         uint2 sah[RB == 0 ? 1 : RB][AV / 4];
-        if (!CH && have_sc) {
+        if (deq) {
 #pragma unroll
             for (int b = 0; b < (RB == 0 ? 1 : RB); ++b)
 #pragma unroll
@@ -370,7 +386,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
             float s1[RB == 0 ? 2 : 1];
 #pragma unroll
             for (int b = 0; b < (RB == 0 ? 2 : 1); ++b)
-                s1[b] = (!CH && have_sc) ? rh2f(wsc[g * COLS + 32 * c + col_of(b)]) * (1.0f / 256.0f) : 0.f;
+                s1[b] = deq ? rh2f(wsc[g * COLS + 32 * c + col_of(b)]) * (1.0f / 256.0f) : 0.f;
             Acc d[NB];
             if constexpr (RB == 0) {
                 uint32_t w[2][4];
@@ -383,7 +399,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
                     d[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[0][0], rfrag(w[b][0], w[b][1]),
-                                                                 CH ? isum[CH ? c : 0][CH ? b : 0] : start, 0, 0, 0);
+                                                                 INT ? isum[INT ? c : 0][INT ? b : 0] : start, 0, 0, 0);
                     d[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[0][1], rfrag(w[b][2], w[b][3]), d[b], 0, 0, 0);
                 }
             } else {
@@ -397,16 +413,22 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
                 for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
                     for (int b = 0; b < RB; ++b) {
-                        if (kk == 0) d[b] = CH ? isum[CH ? c : 0][CH ? b : 0] : start;
+                        if (kk == 0) d[b] = INT ? isum[INT ? c : 0][INT ? b : 0] : start;
                         d[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[b][kk], bw[kk], d[b], 0, 0, 0);
                     }
             }
-            if constexpr (CH) {
+            if constexpr (INT) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) isum[c][b] = d[b];
-            } else {
+            }
+            if constexpr (!CH) {
+                if (WHOLE && ((i + 1) & ((1 << lg) - 1)) != 0) continue;  // uniform: the group goes on
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
+                    if constexpr (WHOLE) {
+#pragma unroll
+                        for (int r = 0; r < AV; ++r) isum[c][b][r] = 0;
+                    }
                     if constexpr (DUMP) {
                         int col = n0 + 32 * c + col_of(b);
                         asm volatile("" : "+v"(col));  // no address is kept from stage to stage (registers)
@@ -419,15 +441,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
                             }
                         }
                         if (!have_sc) continue;
+                        if constexpr (!WHOLE) {
 #pragma unroll
-                        for (int r = 0; r < AV; ++r) d[b][r] += static_cast<int>(MAGIC_BITS);
+                            for (int r = 0; r < AV; ++r) d[b][r] += static_cast<int>(MAGIC_BITS);
+                        }
                     }
                     const float s = s1[RB == 0 ? b : 0], nb = -MAGIC * s;
 #pragma unroll
                     for (int r = 0; r < AV; ++r) {
                         const uint2& pr = sah[RB == 0 ? 0 : b][r >> 2];
                         const uint16_t h = static_cast<uint16_t>((r & 2 ? pr.y : pr.x) >> (16 * (r & 1)));
-                        const float t = fmaf(__int_as_float(d[b][r]), s, nb);
+                        const float t = WHOLE ? static_cast<float>(d[b][r]) * s : fmaf(__int_as_float(d[b][r]), s, nb);
                         acc[c][AV * b + r] = fmaf(t, rh2f(h), acc[c][AV * b + r]);
                     }
                 }
@@ -437,7 +461,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     for (int q0 = 0; q0 < n; q0 += PF)
         unroll<PF>([&](auto J) __attribute__((always_inline)) {
             constexpr int j = decltype(J)::value;
-            if (wave + NW * (q0 + j) < nks) process(J, q0 + j);  // uniform: no stage past K (its scales are not there)
+            if (q0 + j < n && stage_of(q0 + j) < nks) process(J, q0 + j);  // uniform: no stage past K (its scales are not there)
             __builtin_amdgcn_sched_barrier(0);  // the stage's registers are read before its slot is loaded again
             load(J, q0 + j + PF);
         });
@@ -506,11 +530,11 @@ int64_t rows_lds_bytes(int64_t K, int64_t G, int nw, bool fuse) {
     return front > red ? front : red;
 }
 
-template <int RB, int CT, int NW, int PF, int OCC, bool NT, bool CH, bool DUMP, int QL>
+template <int RB, int CT, int NW, int PF, int OCC, bool NT, int MODE, bool DUMP, int QL>
 hipError_t launch_one(const Args& a) {
     using F = Form<RB, CT>;
     static std::atomic<uint64_t> lds_allowed{0};
-    const void* k = reinterpret_cast<const void*>(w4a4_rows_kernel<RB, CT, NW, PF, OCC, NT, CH, DUMP, QL>);
+    const void* k = reinterpret_cast<const void*>(w4a4_rows_kernel<RB, CT, NW, PF, OCC, NT, MODE, DUMP, QL>);
     const hipError_t e = allow_dynamic_lds(k, ROWS_LDS, lds_allowed);
     if (e != hipSuccess) return e;
     const int64_t lds = rows_lds_bytes<RB, CT>(a.K, a.G, NW, QL > 0);
@@ -520,7 +544,7 @@ hipError_t launch_one(const Args& a) {
         for (lg = 0; (int64_t{128} << lg) < a.G; ++lg) {
         }
     const dim3 grid(static_cast<unsigned>(((a.N + F::COLS - 1) / F::COLS + 7) / 8 * 8 * ((a.M + F::ROWS - 1) / F::ROWS)));
-    hipLaunchKernelGGL((w4a4_rows_kernel<RB, CT, NW, PF, OCC, NT, CH, DUMP, QL>), grid, dim3(64 * NW),
+    hipLaunchKernelGGL((w4a4_rows_kernel<RB, CT, NW, PF, OCC, NT, MODE, DUMP, QL>), grid, dim3(64 * NW),
                        static_cast<size_t>(lds), a.stream, a.Aq, a.sa, a.Wq, a.sw, static_cast<int>(a.M),
                        static_cast<int>(a.N), static_cast<int>(a.K), lg, static_cast<int>(a.K / a.G), a.Y, a.wt ? 1 : 0,
                        a.x, a.aq_out, a.sa_out, a.dump.P, a.dump.m0, a.dump.mr);
@@ -532,23 +556,26 @@ hipError_t launch_one(const Args& a) {
 enum RowsForm : int { kR16, kR32, kR32x2, kR32x2w4, kR64, kR64w4 };
 
 // (DUMP: a shorter ring where the registers run out.)
-template <bool NT, bool CH, bool DUMP>
+template <bool NT, int MODE, bool DUMP>
 hipError_t launch_form(RowsForm f, const Args& a) {
-    switch (f) {
-        case kR16: return launch_one<0, 1, 8, 2, 4, NT, CH, DUMP, 0>(a);
-        case kR32: return launch_one<1, 1, 8, 2, DUMP ? 2 : 4, NT, CH, DUMP, 0>(a);
-        case kR32x2: return launch_one<1, 2, 8, 2, 2, NT, CH, DUMP, 0>(a);
-        case kR32x2w4: return launch_one<1, 2, 4, 2, 2, NT, CH, DUMP, 0>(a);
-        default: break;
+    if constexpr (MODE != kWhole) {  // more than 32 rows only
+        if (f == kR16) return launch_one<0, 1, 8, 2, 4, NT, MODE, DUMP, 0>(a);
+        if (f == kR32) return launch_one<1, 1, 8, 2, DUMP ? 2 : 4, NT, MODE, DUMP, 0>(a);
     }
+    if (f == kR32x2) return launch_one<1, 2, 8, 2, 2, NT, MODE, DUMP, 0>(a);
+    if (f == kR32x2w4) return launch_one<1, 2, 4, 2, 2, NT, MODE, DUMP, 0>(a);
     if constexpr (!NT) {
-        if (f == kR64) return launch_one<2, 2, 8, DUMP ? 1 : 2, 2, false, CH, DUMP, 0>(a);
-        if (f == kR64w4) return launch_one<2, 2, 4, DUMP ? 1 : 2, 2, false, CH, DUMP, 0>(a);
+        if (f == kR64) return launch_one<2, 2, 8, DUMP ? 1 : 2, 2, false, MODE, DUMP, 0>(a);
+        if (f == kR64w4) return launch_one<2, 2, 4, DUMP ? 1 : 2, 2, false, MODE, DUMP, 0>(a);
     }
     return hipErrorInvalidValue;
 }
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Past 32 rows a group of several stages is one wave's, so that its sum meets
+// the scales once, whole.
+bool rows_whole(int64_t M, int64_t K, int64_t G) { return M > 32 && G > 128 && G != K; }
 
 // Time in us of the 64-column forms on 256 CUs at G = 128 (launch, prologue and
 // reduction, then per round of workgroups a start and a time per 128-wide
@@ -556,15 +583,30 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // K = 1024 .. 28672 on MI355X, within 20 % of each.  load: workgroups on the
 // busiest CU; a CU with one runs it with eight waves, with more they have four
 // and two or three at a time hide each other's start and end.
-// Per channel (ch): no dequantization in the loop; 190 shapes.
-double cost32(int64_t M, int64_t N, int64_t K, bool ch) {
+// Per channel: no dequantization in the loop; 190 shapes.
+// Whole groups (G = 256, 512, 1024): n counts the stages of the wave with the
+// most groups, times the waves; 415 shapes, N = 512 .. 57344, within 40 % of
+// 32-row and 60 % of 64-row times (the choice by them: rows_take).
+double whole_stages(int64_t K, int64_t G, double load) {
+    const int64_t waves = load == 1.0 ? 8 : 4;
+    return static_cast<double>(waves * cdiv(K / G, waves) * (G / 128));
+}
+double cost32(int64_t M, int64_t N, int64_t K, int64_t G) {
     const double n = static_cast<double>(kstages(K)), load = static_cast<double>(cdiv(cdiv(M, 32) * cdiv(N, 64), device_cu_count()));
-    if (ch) return load == 1.0 ? 4.6 + 0.094 * n : 3.6 + load * (0.68 + 0.092 * n);
+    if (rows_whole(M, K, G)) {
+        const double nw = whole_stages(K, G, load);
+        return load == 1.0 ? 3.6 + 0.112 * nw : 4.5 + load * (0.19 + 0.115 * nw);
+    }
+    if (G == K) return load == 1.0 ? 4.6 + 0.094 * n : 3.6 + load * (0.68 + 0.092 * n);
     return load == 1.0 ? 4.3 + 0.116 * n : 2.8 + load * (0.74 + 0.118 * n);
 }
-double cost64(int64_t M, int64_t N, int64_t K, bool ch) {
+double cost64(int64_t M, int64_t N, int64_t K, int64_t G) {
     const double n = static_cast<double>(kstages(K)), load = static_cast<double>(cdiv(cdiv(M, 64) * cdiv(N, 64), device_cu_count()));
-    if (ch) return load == 1.0 ? 5.1 + 0.167 * n : 5.0 + load * (1.36 + 0.155 * n);
+    if (rows_whole(M, K, G)) {
+        const double nw = whole_stages(K, G, load);
+        return load == 1.0 ? 5.0 + 0.165 * nw : 5.3 + load * (1.32 + 0.166 * nw);
+    }
+    if (G == K) return load == 1.0 ? 5.1 + 0.167 * n : 5.0 + load * (1.36 + 0.155 * n);
     return load == 1.0 ? 6.2 + 0.192 * n : 4.2 + load * (1.76 + 0.189 * n);
 }
 
@@ -581,7 +623,7 @@ RowsForm rows_form(int64_t M, int64_t N, int64_t K, int64_t G) {
     const int64_t cus = device_cu_count();
     if (M <= 16) return kR16;
     if (M <= 32 && (cdiv(N, 32) <= cus || rows_lds_bytes<1, 2>(K, G, 8, false) > ROWS_LDS)) return kR32;
-    if (M > 32 && cost64(M, N, K, G == K) < cost32(M, N, K, G == K)) return cdiv(M, 64) * cdiv(N, 64) <= cus ? kR64 : kR64w4;
+    if (M > 32 && cost64(M, N, K, G) < cost32(M, N, K, G)) return cdiv(M, 64) * cdiv(N, 64) <= cus ? kR64 : kR64w4;
     return cdiv(M, 32) * cdiv(N, 64) <= cus ? kR32x2 : kR32x2w4;
 }
 
@@ -609,7 +651,7 @@ bool rows_fits(int64_t M, int64_t N, int64_t K, int64_t G) {
 }
 
 double rows_cost_us(int64_t M, int64_t N, int64_t K, int64_t G) {
-    const double a = cost32(M, N, K, G == K), b = cost64(M, N, K, G == K);
+    const double a = cost32(M, N, K, G), b = cost64(M, N, K, G);
     return a < b ? a : b;
 }
 
@@ -618,18 +660,20 @@ hipError_t launch_gemm_rows(const uint8_t* Aq, const uint16_t* sa, const uint8_t
     if (!rows_fits(M, N, K, G)) return hipErrorInvalidValue;
     const Args a{Aq, sa, Wq, sw, M, N, K, G, Y, wt, nullptr, nullptr, nullptr, dump, stream};
     const RowsForm f = rows_form(M, N, K, G);
-    const bool ch = G == K;
+    const bool ch = G == K, whole = rows_whole(M, K, G);
     if (dump.P) {
-        if (!ch) {  // stage partials are added atomically into a zeroed window
+        if (!ch) {  // sums are added atomically into a zeroed window
             const hipError_t e = launch_fill_i32(dump.P, static_cast<int64_t>(dump.mr) * N * (K / G), 0, stream);
             if (e != hipSuccess) return e;
         }
-        return ch ? launch_form<false, true, true>(f, a) : launch_form<false, false, true>(f, a);
+        if (ch) return launch_form<false, kChan, true>(f, a);
+        return whole ? launch_form<false, kWhole, true>(f, a) : launch_form<false, kStage, true>(f, a);
     }
-    const bool one_block = f == kR16 || M <= 32;  // every weight is read by one workgroup
-    const bool nt = one_block && N * (K / 2) >= ROWS_NT_BYTES;
-    if (nt) return ch ? launch_form<true, true, false>(f, a) : launch_form<true, false, false>(f, a);
-    return ch ? launch_form<false, true, false>(f, a) : launch_form<false, false, false>(f, a);
+    const bool one_block = M <= 32;  // every weight is read by one workgroup
+    if (one_block && N * (K / 2) >= ROWS_NT_BYTES)
+        return ch ? launch_form<true, kChan, false>(f, a) : launch_form<true, kStage, false>(f, a);
+    if (ch) return launch_form<false, kChan, false>(f, a);
+    return whole ? launch_form<false, kWhole, false>(f, a) : launch_form<false, kStage, false>(f, a);
 }
 
 // The one-row linear on tiled weights with the quantizer in the prologue.
@@ -641,8 +685,8 @@ bool rows_fused_fits(int64_t M, int64_t N, int64_t K, int64_t G) {
 namespace {
 template <int QL>
 hipError_t launch_fused_g(const Args& a, bool nt) {
-    if (a.dump.P) return launch_one<0, 1, 8, 2, 4, false, false, true, QL>(a);
-    return nt ? launch_one<0, 1, 8, 2, 4, true, false, false, QL>(a) : launch_one<0, 1, 8, 2, 4, false, false, false, QL>(a);
+    if (a.dump.P) return launch_one<0, 1, 8, 2, 4, false, kStage, true, QL>(a);
+    return nt ? launch_one<0, 1, 8, 2, 4, true, kStage, false, QL>(a) : launch_one<0, 1, 8, 2, 4, false, kStage, false, QL>(a);
 }
 }  // namespace
 

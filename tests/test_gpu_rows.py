@@ -133,3 +133,56 @@ def test_rows_non_finite_scale(O, M, N, K, G, value):
         Y = host(Y)
         check_tolerance(Y[~bad], y[~bad]) if M > 1 else None
         assert np.array_equal(Y[bad], y[bad].astype(np.float16), equal_nan=True)
+
+
+# groups of several 128-wide stages at 33 rows and more: 32- and 64-row forms of
+# eight and of four waves, group counts that the waves share evenly and not
+WHOLE = [(33, 200, 2048, 256), (72, 1000, 5120, 512), (40, 8200, 9216, 1024), (200, 4096, 8192, 512), (255, 2000, 4096, 256),
+         (64, 520, 3072, 1024), (130, 1000, 28672, 1024), (72, 8192, 2048, 256), (128, 20470, 8192, 256)]
+
+
+@pytest.mark.parametrize("M,N,K,G", WHOLE)
+def test_rows_group_sums_whole(O, M, N, K, G):
+    """A group's sum is added up in integers before it meets its scales, also
+    where several 128-wide stages make up a group.
+
+      * Opposite halves: every group's first half sums to several thousand and
+        its second half takes nearly all of it away again.  Scaled by halves in
+        binary32, the two would leave errors of 2^-24 of the halves, hundreds
+        of times 2^-24 of the result (2 to 20 % of the roundings below differ
+        then); whole, Y is the binary16 rounding of the exact value but where
+        that lies within about 2^-24 (K/G + 8) of a tie: 2^-12 (K/G + 8) of
+        the results at most, and errors add up in a walk, so far fewer.
+      * An infinite activation scale gives infinities by the sign of the whole
+        group's sum."""
+    m = pk()
+    plan = m.apex4_w4a4_gemm_plan("gemm", M, N, K, G)
+    log(f"rows whole groups M={M} N={N} K={K} G={G}: {plan}")
+    assert plan[0] == "decode"
+    r = np.random.default_rng(M + N + K + G)
+    rows = np.unique([0, 31, 32, M // 2, min(63, M - 1), min(64, M - 1), M - 1])
+    half = G // 2
+    a = r.integers(4, 8, (M, K // G, G), dtype=np.int8)
+    w = r.integers(4, 8, (N, K // G, G), dtype=np.int8)
+    a[:, :, half:] = -a[:, :, :half]
+    w[:, :, half:] = w[:, :, :half]
+    k = r.integers(0, half, (M, K // G, 1))
+    np.put_along_axis(a, k, np.take_along_axis(a, k, 2) - np.int8(1), 2)   # one code of each group differs
+    pack = lambda v: ((v[..., 0::2] & 0xF) | ((v[..., 1::2] & 0xF) << 4)).astype(np.uint8).reshape(len(v), K // 2)
+    Aq, Wq = pack(a), pack(w)
+    del a, w
+    sa, sw = wl.random_scales(r, M, K // G), wl.random_scales(r, N, K // G)
+    y = formula(O, Aq[rows], sa[rows], Wq, sw, K, G)
+    d = [dev(v) for v in (Aq, sa, Wq, sw)]
+    Y = host(m.apex4_w4a4_gemm(*d, G))[rows]
+    check_tolerance(Y, y, f"whole groups {M}x{N}x{K} G{G}")
+    wrong = (Y != y.astype(np.float16)).mean()
+    log(f"  roundings that differ: {wrong:.2e}")
+    assert wrong < 2e-3
+
+    Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
+    sa[M // 2, 0] = np.inf
+    y = formula(O, Aq[[M // 2]], sa[[M // 2]], Wq, sw, K, G)
+    Y = host(m.apex4_w4a4_gemm(dev(Aq), dev(sa), dev(Wq), d[3], G))
+    assert np.array_equal(Y[[M // 2]], y.astype(np.float16), equal_nan=True)
+    assert np.isfinite(np.delete(Y, M // 2, 0)).all()

@@ -24,7 +24,8 @@ FLAGS = {
     "w4a4_gemm_pp_kernel": (0, None),
     "w4a4_decode_kernel": (3, 4),
     "w4a4_gemv_kernel": (2, None),
-    "w4a4_gemv_tiled_kernel": (2, None),
+    "w4a4_gemv_tiled_kernel": (0, None),
+    "w4a4_rows_kernel": (7, None),
 }
 
 
@@ -51,7 +52,7 @@ def _template_args(demangled):
 def test_every_kernel_reported(kernels):
     names = {_template_args(d)[0] for d in kernels}
     for k in ("w4a4_gemm_kernel", "w4a4_gemm_pp_kernel", "w4a4_decode_kernel", "w4a4_gemv_kernel",
-              "w4a4_gemv_tiled_kernel", "tile_weights_kernel"):
+              "w4a4_gemv_tiled_kernel", "w4a4_rows_kernel", "tile_weights_kernel"):
         assert k in names, k
     assert all("scratch" in v and "vgpr" in v for v in kernels.values())
 
