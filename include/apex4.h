@@ -180,9 +180,8 @@ int apex4_w4a4_gemm_debug(const uint8_t* A_q, const void* s_a,
 /*
  * The GEMM kernel that `entry` runs for this shape on the current device, and
  * its split over K (*splits = S > 1 only for APEX4_ENTRY_GEMM_WS and
- * APEX4_ENTRY_LINEAR_WS, whose workspace size query then returns S M N 4 bytes;
- * APEX4_KERNEL_DECODE adds its parts inside the workgroups and leaves that
- * workspace unused).  flags as in
+ * APEX4_ENTRY_LINEAR_WS, whose workspace size query then returns S M N 4
+ * bytes).  flags as in
  * apex4_w4a4_gemm_debug (APEX4_DEBUG_W_TILED: the tiled entry points;
  * APEX4_ENTRY_LINEAR and APEX4_ENTRY_LINEAR_WS take no APEX4_DEBUG_GENERAL_TILES).  M == 0 gives kernel 0,
  * splits 0.  Shape and group rules as apex4_w4a4_gemm; unknown entry or flags:
@@ -306,7 +305,7 @@ int apex4_w4a4_linear_debug(const void* x, const uint8_t* W_q, const void* s_w,
  * segment order by the workgroup that finishes last (counters cleared by a
  * kernel on every call, so a captured call replays).  Where the few-row kernel
  * of apex4_w4a4_gemm (fewer than 256 rows) is faster than either, it runs and
- * leaves the workspace unused.  Y is within the tolerance of apex4_w4a4_gemm
+ * needs no workspace.  Y is within the tolerance of apex4_w4a4_gemm
  * (the fp32 summation order differs; for G == K the split over K gives the
  * same bits), deterministic for a given shape and device.
  *

@@ -104,7 +104,7 @@ bool decode_fits(int64_t M, int64_t N, int64_t K, int64_t G);
 // through the workspace in a fixed order (decode_split_workspace_bytes is 0
 // where it does not apply).
 int64_t decode_split_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t G);
-// Whether that form is also the faster one (the workspace stays required).
+// Whether that form is also the faster one.
 bool decode_split_pays(int64_t M, int64_t N, int64_t K, int64_t G);
 hipError_t launch_gemm_decode(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq,
                               const uint16_t* sw, int64_t M, int64_t N, int64_t K, int64_t G,

@@ -1229,11 +1229,12 @@ int splitk_factor(int64_t M, int64_t N, int64_t K, int64_t G) {
     return S;
 }
 
+// What the kernel of plan_gemm uses, and no more.
 int64_t splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t G) {
-    // few rows: the stream-K form of the few-row kernel where it applies
-    if (M > 0 && !gemv_fits(M, N, K, G) && decode_fits(M, N, K, G)) return decode_split_workspace_bytes(M, N, K, G);
-    const int S = splitk_factor(M, N, K, G);
-    return S > 1 ? static_cast<int64_t>(S) * M * N * 4 : 0;
+    if (M <= 0) return 0;
+    const GemmPlan plan = plan_gemm(M, N, K, G, true, false);
+    if (plan.kernel == kKernelDecodeSplit) return decode_split_workspace_bytes(M, N, K, G);
+    return plan.splits > 1 ? static_cast<int64_t>(plan.splits) * M * N * 4 : 0;
 }
 
 hipError_t launch_splitk_reduce(const float* part, int S, int64_t MN, uint16_t* Y, hipStream_t stream) {
@@ -1297,16 +1298,16 @@ bool rows_take(int64_t M, int64_t N, int64_t K, int64_t G, int S) {
 // 32 rows: the few-row kernels (G >= 128 or per channel: the one of
 // gemm_w4a4_rows.hip; finer groups, and the stream-K form of the workspace
 // path: the persistent one).  Below kRowsMax rows: the few-row kernel or the
-// tile kernels by cost; the few-row kernel splits K over the waves of a
-// workgroup and leaves the workspace unused, whose size (splits) stays that of
-// the tile kernels' split.
+// tile kernels by cost.  A split over K that the few-row kernel beats is not
+// made, under force_tile neither, and needs no workspace; the choice is then
+// that without a workspace.
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G, bool split, bool force_tile, bool wt) {
-    const int S = split ? splitk_factor(M, N, K, G) : 1;
+    int S = split ? splitk_factor(M, N, K, G) : 1;
+    if (S > 1 && rows_take(M, N, K, G, S)) S = 1;
     if (!force_tile) {
         if (gemv_fits(M, N, K, G, wt)) return {kKernelGemv, 1};
         if (split && !gemv_fits(M, N, K, G) && decode_split_pays(M, N, K, G)) return {kKernelDecodeSplit, 1};
-        if (rows_take(M, N, K, G, S)) return {kKernelDecode, S};
-        if (decode_fits(M, N, K, G)) return {kKernelDecode, 1};
+        if ((S == 1 && rows_take(M, N, K, G, 1)) || decode_fits(M, N, K, G)) return {kKernelDecode, 1};
     }
     if (S > 1) return {G == 128 && !force_tile ? kKernelPingPong : kKernelTile64, S};
     const int64_t big_tiles = ((M + 127) / 128) * ((N + 255) / 256);
@@ -1344,8 +1345,7 @@ hipError_t launch_gemm_splitk(const uint8_t* Aq, const uint16_t* sa, const uint8
     const GemmPlan plan = plan_gemm(M, N, K, G, true, force_tile, wt);
     if (plan.kernel == kKernelDecodeSplit)  // the workspace holds the stream-K counters and parts
         return launch_planned(plan, Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, part, wt);
-    if (plan.splits < 2 || plan.kernel == kKernelDecode)
-        return launch_planned(plan, Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, nullptr, wt);
+    if (plan.splits < 2) return launch_planned(plan, Aq, sa, Wq, sw, M, N, K, G, Y, stream, dump, nullptr, wt);
     const int S = plan.splits;
     // split ranges hold whole groups, so every group sum except the
     // per-channel one is dumped by the kernel that completes it

@@ -1,0 +1,74 @@
+"""The kernel choice of the GEMM, on the CPU (no GPU needed: without one the
+library plans for 256 compute units).  The choice has no entry point that works
+without a device, so the library's own functions are called by their C++ names.
+
+Over seeded shapes of every group size:
+  * a workspace is asked for exactly where the chosen kernel uses one, and
+    where none is, the choice is the one without a workspace;
+  * the few-row kernel is only chosen for shapes that it takes.
+"""
+import ctypes
+import random
+
+import pytest
+
+I = ctypes.c_int64
+GEMV, DECODE, TILE64, TILE128, PINGPONG, DECODE_SPLIT = 1, 3, 4, 5, 6, 7
+
+
+class Plan(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int), ("splits", ctypes.c_int)]
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2606_08761_amd as m
+    L = m.lib()
+
+    def fn(name, restype, *more):
+        f = getattr(L, name)
+        f.restype, f.argtypes = restype, [I] * 4 + list(more)
+        return f
+    b = ctypes.c_bool
+    plan = fn("_ZN5apex49plan_gemmEllllbbb", Plan, b, b, b)
+    return {"plan": lambda M, N, K, G, split, wt=False: (lambda p: (p.kernel, p.splits))(plan(M, N, K, G, split, False, wt)),
+            "workspace": fn("_ZN5apex422splitk_workspace_bytesEllll", I),
+            "rows_fits": fn("_ZN5apex49rows_fitsEllll", b)}
+
+
+def shapes(n, seed):
+    r = random.Random(seed)
+    while n:
+        G = r.choice([32, 64, 128, 256, 512, 1024, 0])
+        M, N = round(2 ** (11 * r.random())), round(2 ** (16 * r.random()))
+        K = 32 * r.randint(1, 2048) if G in (0, 32) else G * r.randint(1, 65536 // G)
+        yield M, N, K, G or K
+        n -= 1
+
+
+def test_workspace_is_what_the_kernel_uses(lib):
+    kernels = set()
+    for M, N, K, G in shapes(20000, 1):
+        kernel, S = lib["plan"](M, N, K, G, True)
+        need = lib["workspace"](M, N, K, G)
+        at = (M, N, K, G, kernel, S, need)
+        kernels.add((kernel, S > 1))
+        if S > 1:
+            assert kernel in (TILE64, PINGPONG) and need == S * M * N * 4, at
+        elif kernel == DECODE_SPLIT:
+            assert need > 0, at
+        else:
+            assert need == 0 and lib["plan"](M, N, K, G, False) == (kernel, 1), at
+    assert kernels == {(GEMV, False), (DECODE, False), (DECODE_SPLIT, False), (TILE64, False), (TILE64, True),
+                       (TILE128, False), (PINGPONG, False), (PINGPONG, True)}
+
+
+def test_few_row_kernel_takes_what_it_is_chosen_for(lib):
+    for M, N, K, G in shapes(20000, 2):
+        for wt in (False, True) if G >= 128 else (False,):
+            for split in (False, True):
+                kernel, _ = lib["plan"](M, N, K, G, split, wt)
+                if kernel == DECODE and G >= 128:
+                    assert lib["rows_fits"](M, N, K, G), (M, N, K, G, wt, split)
+                if kernel == DECODE:
+                    assert M < 256, (M, N, K, G)

@@ -332,7 +332,7 @@ def test_w4a4_linear_module(O):
     import torch
     m = pk()
     N, K, G = 1024, 2048, 128
-    x, w = wl.float_workload("tiny", 64, N, K)
+    x, w = wl.float_workload("tiny", 300, N, K)
     Wq_o, sw_o = O.quantize(w, G)
     lin = m.W4A4Linear(dev(w), G)
     lin_r = m.W4A4Linear(dev(w), G, layout="rows")
@@ -340,19 +340,19 @@ def test_w4a4_linear_module(O):
     assert np.array_equal(_untile(host(lin.W_t), N, K), Wq_o)
     assert np.array_equal(host(lin_r.W_q), Wq_o)
     stream = torch.cuda.current_stream()
-    # same shape twice (buffers reused), then others; 64 rows take the split-K
-    # GEMM with the layer's own workspace
-    for rows in (24, 24, 7, 64):
+    # same shape twice (buffers reused), then others; 300 rows take the split-K
+    # GEMM with the layer's own workspace, 64 the few-row kernel without one
+    for rows in (24, 24, 7, 64, 300):
         xb = x[:rows]
         y = lin(dev(xb).reshape(1, rows, K))
         yr = lin_r(dev(xb).reshape(1, rows, K))
         torch.cuda.synchronize()
         assert y.shape == (1, rows, N)
         assert torch.equal(y, yr)                  # rows > 1: the same bits from either layout
-        assert (lin._work[(rows, stream.cuda_stream)][2] is not None) == (rows == 64)
+        assert (lin._work[(rows, stream.cuda_stream)][2] is not None) == (rows == 300)
         Aq_o, sa_o = O.quantize(xb, G)
         check_tolerance(host(y)[0], O.gemm_rows(Aq_o, sa_o, Wq_o, sw_o, K, G), f"module rows={rows}")
-    assert len(lin._work) == 3
+    assert len(lin._work) == 4
     # one row (the one-row kernels) through both layouts
     y1, y1r = host(lin(dev(x[:1]))), host(lin_r(dev(x[:1])))
     Aq_o, sa_o = O.quantize(x[:1], G)
@@ -377,7 +377,8 @@ def test_w4a4_linear_module_streams(O):
     buffers: both results are right although the streams overlap."""
     import torch
     m = pk()
-    N, K, G, rows = 2048, 4096, 128, 64
+    N, K, G, rows = 2048, 4096, 128, 256
+    assert m.apex4_w4a4_gemm_plan("linear_ws", rows, N, K, G)[1] > 1
     x, w = wl.float_workload("tiny", 2 * rows, N, K)
     lin = m.W4A4Linear(dev(w), G)
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
@@ -436,9 +437,9 @@ def test_w4a4_linear_module_graph(O):
 def test_weights_just_under_4gib(O):
     """The largest weight operand the ABI accepts: N K/2 = 4,294,950,912 bytes,
     16 KiB under 2^32 (the kernels address operand rows with 32-bit byte
-    offsets).  One row (dot-product kernel), 8 rows (decode kernel) and 40
-    rows (tile kernel), checked on sampled output columns that include the
-    last rows of W."""
+    offsets).  One row (dot-product kernel), 8 and 40 rows (few-row kernel)
+    and 256 rows (tile kernel), checked on sampled output columns that include
+    the last rows of W."""
     import torch
     m = pk()
     N, K, G = 262143, 32768, 128
@@ -451,8 +452,9 @@ def test_weights_just_under_4gib(O):
     cols = np.unique(np.concatenate([np.arange(8), np.arange(N - 8, N), r.integers(0, N, size=24)]))
     Wq_s, sw_s = Wq[cols], sw[cols]
     del Wq
-    for M in (1, 8, 40):
+    for M, kern in ((1, "gemv"), (8, "decode"), (40, "decode"), (256, "pingpong")):
         log(f"4 GiB weights: M={M}")
+        assert m.apex4_w4a4_gemm_plan("gemm", M, N, K, G) == (kern, 1)
         Aq, sa = wl.random_codes(r, M, K), wl.random_scales(r, M, K // G)
         Y = host(m.apex4_w4a4_gemm(dev(Aq), dev(sa), Wq_d, sw_d, G))
         assert Y.shape == (M, N)

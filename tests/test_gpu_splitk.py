@@ -33,16 +33,17 @@ def operands(M, N, K, seed):
 
 # (M, N, K): split factors 8, 4 and 2, ragged tiles (M = 260: a 4-row tile),
 # odd M N (the reduction's one-element path), 4 stages per split
-SPLIT = [(33, 8192, 8192), (64, 8192, 8192), (256, 8192, 8192), (512, 8192, 4096), (100, 1000, 2048),
-         (130, 4100, 2048), (65, 1001, 2048), (200, 2000, 2048), (260, 6144, 8192)]
+SPLIT = [(256, 4096, 8192), (256, 8192, 8192), (512, 8192, 4096), (1000, 1000, 2048),
+         (300, 4100, 2048), (257, 1001, 2048), (256, 1000, 1024), (260, 6144, 8192)]
 
 
 @pytest.mark.parametrize("M,N,K", SPLIT)
 def test_split_matches_oracle(O, M, N, K):
     m = pk()
     need = m.apex4_w4a4_gemm_workspace_size(M, N, K, G)
-    log(f"split-K M={M} N={N} K={K} workspace={need}")
-    assert need > 0 and need % (4 * M * N) == 0 and need // (4 * M * N) in (2, 4, 8)
+    kern, S = m.apex4_w4a4_gemm_plan("gemm_ws", M, N, K, G)
+    log(f"split-K M={M} N={N} K={K}: {kern} S={S} workspace={need}")
+    assert kern == "pingpong" and S in (2, 4, 8) and need == S * 4 * M * N
     Aq, sa, Wq, sw = operands(M, N, K, M * 131 + N + K)
     d = [dev(a) for a in (Aq, sa, Wq, sw)]
     import torch
@@ -56,13 +57,17 @@ def test_split_matches_oracle(O, M, N, K):
 
 @pytest.mark.parametrize("M,N,K,GG", [(2048, 8192, 1024, 128), (16, 8192, 1024, 128), (1, 4096, 1024, 128),
                                       (256, 8192, 1024, 64), (256, 8192, 1024, 1024), (64, 1024, 384, 128),
-                                      (64, 28672, 1024, 128)])
+                                      (64, 28672, 1024, 128), (64, 8192, 8192, 128), (200, 1000, 4096, 256),
+                                      (64, 2048, 8192, 8192)])
 def test_no_split_is_the_plain_gemm(M, N, K, GG):
     """No workspace needed: the same kernels as apex4_w4a4_gemm run (K = 384 has
     too few stages per split; with G != 128 at M = 256, N = 8192 the small tiles
-    already fill the CUs; M = 64 with N = 28672 would only split in two)."""
+    already fill the CUs; M = 64 with N = 28672 would only split in two; the
+    few-row kernel beats the split at 64 and 200 rows)."""
     m = pk()
     assert m.apex4_w4a4_gemm_workspace_size(M, N, K, GG) == 0
+    assert m.apex4_w4a4_gemm_plan("gemm_ws", M, N, K, GG) == m.apex4_w4a4_gemm_plan("gemm", M, N, K, GG)
+    assert m.apex4_w4a4_gemm_plan("gemm_ws", M, N, K, GG)[1] == 1
     r = np.random.default_rng(M + N + K + GG)
     Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
     sa, sw = wl.random_scales(r, M, K // GG), wl.random_scales(r, N, K // GG)
@@ -75,7 +80,7 @@ def test_no_split_is_the_plain_gemm(M, N, K, GG):
 def test_workspace_refused_when_short():
     import torch
     m = pk()
-    M, N, K = 64, 8192, 8192
+    M, N, K = 256, 4096, 8192
     need = m.apex4_w4a4_gemm_workspace_size(M, N, K, G)
     Aq, sa, Wq, sw = operands(M, N, K, 5)
     d = [dev(a) for a in (Aq, sa, Wq, sw)]
@@ -87,8 +92,9 @@ def test_workspace_refused_when_short():
 
 # the general tile kernel split over K: fine groups, persisting groups (splits
 # on group boundaries), per-channel (exact int32 partials)
-SPLIT_G = [(256, 1024, 8192, 32), (128, 2048, 4096, 64), (200, 1000, 4096, 256), (100, 1000, 2048, 1024),
-           (65, 1001, 2048, 32), (64, 2048, 8192, 8192), (300, 520, 3072, 3072)]
+SPLIT_G = [(256, 1024, 8192, 32), (128, 2048, 4096, 64), (256, 1024, 8192, 256), (300, 1000, 4096, 256),
+           (257, 1001, 4096, 512), (256, 1000, 4096, 1024), (300, 520, 8192, 1024),
+           (65, 1001, 2048, 32), (256, 2048, 8192, 8192), (300, 520, 3072, 3072)]
 
 
 @pytest.mark.parametrize("M,N,K,GG", SPLIT_G)
@@ -96,8 +102,9 @@ def test_split_other_groups(O, M, N, K, GG):
     import torch
     m = pk()
     need = m.apex4_w4a4_gemm_workspace_size(M, N, K, GG)
-    log(f"split-K M={M} N={N} K={K} G={GG} workspace={need}")
-    assert need > 0 and need // (4 * M * N) in (2, 4, 8)
+    kern, S = m.apex4_w4a4_gemm_plan("gemm_ws", M, N, K, GG)
+    log(f"split-K M={M} N={N} K={K} G={GG}: {kern} S={S} workspace={need}")
+    assert kern == "tile64" and S in (2, 4, 8) and need == S * 4 * M * N
     r = np.random.default_rng(M * 7 + N + K + GG)
     Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
     sa, sw = wl.random_scales(r, M, K // GG), wl.random_scales(r, N, K // GG)

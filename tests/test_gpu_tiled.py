@@ -97,7 +97,8 @@ def test_tiled_gemm_equals_row_major(O, M, N, K, G):
 
 
 # split over K (workspace entry): ping-pong and small tiles, per channel
-SPLIT = [(256, 8192, 8192, 128), (128, 2048, 8192, 256), (256, 4096, 8192, 8192), (300, 2000, 4096, 128)]
+SPLIT = [(256, 8192, 8192, 128), (256, 1024, 8192, 256), (260, 1000, 8192, 512), (300, 777, 8192, 1024),
+         (256, 2048, 8192, 8192), (300, 2000, 4096, 128)]
 
 
 @pytest.mark.parametrize("M,N,K,G", SPLIT)
@@ -106,7 +107,7 @@ def test_tiled_split_equals_row_major(O, M, N, K, G):
     m = pk()
     kern, S = m.apex4_w4a4_gemm_plan("gemm_ws", M, N, K, G, m.APEX4_DEBUG_W_TILED)
     log(f"tiled split M={M} N={N} K={K} G={G}: {kern} S={S}")
-    assert S > 1
+    assert kern == ("pingpong" if G == 128 else "tile64") and S > 1
     r = np.random.default_rng(M + N + K + G)
     Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
     sa, sw = wl.random_scales(r, M, K // G), wl.random_scales(r, N, K // G)
