@@ -128,6 +128,8 @@ hipError_t launch_gemv(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq,
 constexpr int64_t kRowsMax = 256;
 bool rows_fits(int64_t M, int64_t N, int64_t K, int64_t G);
 double rows_cost_us(int64_t M, int64_t N, int64_t K, int64_t G);
+// The kernel's form for a shape (RowsForm in gemm_w4a4_rows.hip), for tests.
+int rows_form_of(int64_t M, int64_t N, int64_t K, int64_t G);
 hipError_t launch_gemm_rows(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw, int64_t M,
                             int64_t N, int64_t K, int64_t G, uint16_t* Y, hipStream_t stream, Dump dump = Dump(),
                             bool wt = false);

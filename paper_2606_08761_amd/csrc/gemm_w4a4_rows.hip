@@ -650,6 +650,8 @@ bool rows_fits(int64_t M, int64_t N, int64_t K, int64_t G) {
     return M >= 1 && M < kRowsMax && N >= 1 && g_ok && rows_lds_of(rows_form(M, N, K, G), K, G) <= ROWS_LDS;
 }
 
+int rows_form_of(int64_t M, int64_t N, int64_t K, int64_t G) { return rows_form(M, N, K, G); }
+
 double rows_cost_us(int64_t M, int64_t N, int64_t K, int64_t G) {
     const double a = cost32(M, N, K, G), b = cost64(M, N, K, G);
     return a < b ? a : b;

@@ -1,8 +1,8 @@
 """The few-row kernel (fewer than 256 rows at G >= 128 or per channel): its forms
-of 16, 32 and 64 rows by 32 or 64 columns, at the edges of their rows and
-columns, with fewer stages than waves, with scale rows of every alignment
-(K/G a multiple of 8 or not), sub-group partials and a partial last stage per
-channel.
+of 16 and 32 rows by 32 or 64 columns (SHAPES) and of 64 rows by 64 columns
+(FORMS_64), at the edges of their rows and columns, with fewer stages than
+waves, with scale rows of every alignment (K/G a multiple of 8 or not),
+sub-group partials and a partial last stage per channel.
 
   * Y within the tolerance of the oracle in full, the same bits on both weight
     layouts, through the workspace entry point when it picks the same kernel,
@@ -11,6 +11,8 @@ channel.
   * one row with the quantizer in the prologue (tiled weights): Y and the work
     buffers equal the quantizer followed by the GEMM, bit for bit.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -25,8 +27,8 @@ def pk():
     return m
 
 
-# (M, N, K, G): each form at its first and last row count (16 / 17, 32 / 33,
-# 64 / 65, 255); one column, one past a tile, an odd count of 32-column tiles;
+# (M, N, K, G): the 16- and 32-row forms at the first and last row counts (16 /
+# 17, 32 / 33, 64 / 65, 255); one column, one past a tile, an odd count of 32-column tiles;
 # one stage (seven idle waves), 9 stages, 26 and 27 groups (not a multiple of
 # 8); more column tiles than eight XCDs take evenly; G = 256, 512, 1024; per
 # channel with whole and partial last stages
@@ -37,12 +39,31 @@ SHAPES = [(1, 33, 128, 128), (15, 1, 1152, 128), (16, 1000, 3328, 128), (17, 65,
           (9, 100, 96, 96), (16, 520, 4000, 4000), (32, 1000, 8192, 8192), (40, 65, 4000, 4000), (250, 2000, 1120, 1120)]
 
 
+FORMS = ("16x32", "32x32", "32x64", "32x64 four waves", "64x64", "64x64 four waves")
+
+
+def form(M, N, K, G):
+    """The form that the library chooses (no entry point tells: its own function, by its C++ name)."""
+    f = pk().lib()._ZN5apex412rows_form_ofEllll
+    f.argtypes = [ctypes.c_int64] * 4
+    return FORMS[f(M, N, K, G)]
+
+
+# the form of each of SHAPES on 256 CUs, beside its sizes
+EXPECT = {(15, 1, 1152, 128): 0, (16, 1000, 3328, 128): 0, (17, 65, 1024, 128): 1, (31, 8200, 256, 128): 2,
+          (33, 1000, 3328, 128): 2, (65, 2080, 1024, 128): 2, (96, 16500, 256, 128): 3, (129, 4100, 640, 128): 3,
+          (200, 8200, 512, 128): 3, (32, 1000, 8192, 8192): 1, (250, 2000, 1120, 1120): 2}
+
+
 @pytest.mark.parametrize("M,N,K,G", SHAPES)
 def test_rows(O, M, N, K, G):
     import torch
     m = pk()
     plan, plan_ws = (m.apex4_w4a4_gemm_plan(e, M, N, K, G) for e in ("gemm", "gemm_ws"))
-    log(f"rows M={M} N={N} K={K} G={G}: {plan}, with a workspace {plan_ws}")
+    log(f"rows M={M} N={N} K={K} G={G}: {plan} {form(M, N, K, G)}, with a workspace {plan_ws}")
+    assert M == 1 or plan == ("decode", 1)
+    if (M, N, K, G) in EXPECT:
+        assert form(M, N, K, G) == FORMS[EXPECT[M, N, K, G]]
     r = np.random.default_rng(M * 31 + N * 7 + K + G)
     Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
     sa, sw = wl.random_scales(r, M, K // G), wl.random_scales(r, N, K // G)
@@ -71,6 +92,44 @@ def test_rows(O, M, N, K, G):
     y = O.gemm_rows(Aq, sa, Wq, sw, K, G)
     check_tolerance(host(Y), y, f"rows {M}x{N}x{K} G{G}")
     check_tolerance(host(Yw), y, f"rows with a workspace {M}x{N}x{K} G{G}")
+
+
+# (M, N, K, G, waves): 64 rows by 64 columns, in workgroups of eight and of four
+# waves; one row past a block, two blocks, the last of four; ragged columns (an
+# odd count of 32-column tiles); a stage, a group and the row to a scale, a
+# partial last stage; K/G a multiple of 8 and not
+FORMS_64 = [(65, 8190, 8192, 128, 8), (72, 8190, 8192, 128, 8), (128, 8150, 8320, 128, 8), (255, 16390, 4096, 128, 4),
+            (128, 33000, 4224, 128, 4), (72, 8190, 2048, 256, 8), (128, 20470, 8192, 256, 4), (100, 8190, 8192, 1024, 8),
+            (72, 8190, 4000, 4000, 8), (128, 8150, 2016, 2016, 8), (200, 4096, 4096, 4096, 8), (182, 35473, 1856, 1856, 4)]
+
+
+@pytest.mark.parametrize("M,N,K,G,waves", FORMS_64)
+def test_rows_64(O, M, N, K, G, waves):
+    """Y on sampled rows (both ends of every block) against the oracle, on both
+    weight layouts and from the debug form, and the exact group sums of a window
+    across the first block's end."""
+    import torch
+    m = pk()
+    assert m.apex4_w4a4_gemm_plan("gemm", M, N, K, G) == ("decode", 1)
+    assert form(M, N, K, G) == FORMS[4 if waves == 8 else 5]
+    log(f"rows 64x64 M={M} N={N} K={K} G={G}")
+    r = np.random.default_rng(M * 31 + N * 7 + K + G)
+    Aq, Wq = wl.random_codes(r, M, K), wl.random_codes(r, N, K)
+    sa, sw = wl.random_scales(r, M, K // G), wl.random_scales(r, N, K // G)
+    d = [dev(a) for a in (Aq, sa, Wq, sw)]
+    Wt = m.apex4_tile_weights(d[2])
+    m0, mr = 61, min(8, M - 61)
+    Y = m.apex4_w4a4_gemm(*d, G)
+    Yt = m.apex4_w4a4_gemm_tiled(d[0], d[1], Wt, d[3], G)
+    Yd, P = m.apex4_w4a4_gemm_debug(*d, G, m0, mr)
+    Ydt, Pt = m.apex4_w4a4_gemm_debug(d[0], d[1], Wt, d[3], G, m0, mr, flags=m.APEX4_DEBUG_W_TILED)
+    P2 = m.apex4_w4a4_gemm_groupsums(d[0], d[2], G, m0, mr)
+    torch.cuda.synchronize()
+    assert torch.equal(Yt, Y) and torch.equal(Yd, Y) and torch.equal(Ydt, Y)
+    P_o = O.groupsums(Aq, Wq, K, G, m0, mr)
+    assert all(np.array_equal(host(p), P_o) for p in (P, Pt, P2))
+    rows = np.unique([i for b in range(0, M, 64) for i in (b, b + 15, b + 16, b + 31, b + 32, b + 63) if i < M] + [M - 1])
+    check_tolerance(host(Y)[rows], O.gemm_rows(Aq, sa, Wq, sw, K, G, rows), f"rows 64x64 {M}x{N}x{K} G{G}")
 
 
 @pytest.mark.parametrize("N,K,G", [(1, 256, 128), (33, 3328, 128), (1000, 5120, 256), (9000, 4096, 512), (64, 40960, 128)])
