@@ -47,7 +47,7 @@
 //     waves' sums are added exactly and scaled once (the same bits as the tile
 //     kernels); K % 128 != 0 only occurs here, and pieces past the row's end
 //     are sent out of the descriptor's range, so they read as zero.
-//   * Weights read by one workgroup only (one block of rows) are loaded
+//   * Tiled weights read by one workgroup only (one block of rows) are loaded
 //     nontemporal when they are large: 6 % (N = K = 8192) to 13 % (N = 57344)
 //     faster than with the default policy when they come from HBM, 2 % slower
 //     when they sit in the Infinity Cache.
@@ -627,9 +627,13 @@ RowsForm rows_form(int64_t M, int64_t N, int64_t K, int64_t G) {
     return cdiv(M, 32) * cdiv(N, 64) <= cus ? kR32x2 : kR32x2w4;
 }
 
-// Weights from this size on that one workgroup reads are loaded nontemporal:
-// smaller ones may well still be in the 256 MB Infinity Cache when they are
-// needed again, and their launches are bound by latency anyway.
+// Tiled weights from this size on that one workgroup reads are loaded
+// nontemporal: smaller ones may well still be in the 256 MB Infinity Cache when
+// they are needed again, and their launches are bound by latency anyway.
+// Row-major weights never: a stage is 64 bytes of a row, so a 128-byte line has
+// two stages, of two waves, and the line of a nontemporal load is gone when the
+// second comes (8 rows, N = 2560, K = 28672: 38.0 us so, 23.6 without; 8 rows,
+// N = K = 28672: 157 and 101).
 constexpr int64_t ROWS_NT_BYTES = int64_t{16} << 20;
 
 int64_t rows_lds_of(RowsForm f, int64_t K, int64_t G) {
@@ -657,6 +661,10 @@ double rows_cost_us(int64_t M, int64_t N, int64_t K, int64_t G) {
     return a < b ? a : b;
 }
 
+bool rows_nontemporal(int64_t M, int64_t N, int64_t K, bool wt) {
+    return wt && M <= 32 && N * (K / 2) >= ROWS_NT_BYTES;  // up to 32 rows: every weight is read by one workgroup
+}
+
 hipError_t launch_gemm_rows(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw, int64_t M,
                             int64_t N, int64_t K, int64_t G, uint16_t* Y, hipStream_t stream, Dump dump, bool wt) {
     if (!rows_fits(M, N, K, G)) return hipErrorInvalidValue;
@@ -671,8 +679,7 @@ hipError_t launch_gemm_rows(const uint8_t* Aq, const uint16_t* sa, const uint8_t
         if (ch) return launch_form<false, kChan, true>(f, a);
         return whole ? launch_form<false, kWhole, true>(f, a) : launch_form<false, kStage, true>(f, a);
     }
-    const bool one_block = M <= 32;  // every weight is read by one workgroup
-    if (one_block && N * (K / 2) >= ROWS_NT_BYTES)
+    if (rows_nontemporal(M, N, K, wt))
         return ch ? launch_form<true, kChan, false>(f, a) : launch_form<true, kStage, false>(f, a);
     if (ch) return launch_form<false, kChan, false>(f, a);
     return whole ? launch_form<false, kWhole, false>(f, a) : launch_form<false, kStage, false>(f, a);
@@ -700,7 +707,7 @@ hipError_t launch_rows_fused(const uint16_t* x, const uint8_t* Wt, const uint16_
         const hipError_t e = launch_fill_i32(dump.P, static_cast<int64_t>(dump.mr) * N * (K / G), 0, stream);
         if (e != hipSuccess) return e;
     }
-    const bool nt = N * (K / 2) >= ROWS_NT_BYTES;
+    const bool nt = rows_nontemporal(1, N, K, true);
     if (G == 128) return launch_fused_g<16>(a, nt);
     if (G == 256) return launch_fused_g<32>(a, nt);
     return launch_fused_g<64>(a, nt);

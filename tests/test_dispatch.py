@@ -5,7 +5,8 @@ without a device, so the library's own functions are called by their C++ names.
 Over seeded shapes of every group size:
   * a workspace is asked for exactly where the chosen kernel uses one, and
     where none is, the choice is the one without a workspace;
-  * the few-row kernel is only chosen for shapes that it takes.
+  * the few-row kernel is only chosen for shapes that it takes, and loads
+    weights past the caches (nontemporal) only where they are tiled and read once.
 """
 import ctypes
 import random
@@ -33,7 +34,14 @@ def lib():
     plan = fn("_ZN5apex49plan_gemmEllllbbb", Plan, b, b, b)
     return {"plan": lambda M, N, K, G, split, wt=False: (lambda p: (p.kernel, p.splits))(plan(M, N, K, G, split, False, wt)),
             "workspace": fn("_ZN5apex422splitk_workspace_bytesEllll", I),
-            "rows_fits": fn("_ZN5apex49rows_fitsEllll", b)}
+            "rows_fits": fn("_ZN5apex49rows_fitsEllll", b),
+            "nontemporal": _nontemporal(L)}
+
+
+def _nontemporal(L):
+    f = L._ZN5apex416rows_nontemporalElllb
+    f.restype, f.argtypes = ctypes.c_bool, [I] * 3 + [ctypes.c_bool]
+    return f
 
 
 def shapes(n, seed):
@@ -72,3 +80,10 @@ def test_few_row_kernel_takes_what_it_is_chosen_for(lib):
                     assert lib["rows_fits"](M, N, K, G), (M, N, K, G, wt, split)
                 if kernel == DECODE:
                     assert M < 256, (M, N, K, G)
+
+
+def test_few_row_kernel_streams_tiled_weights_only(lib):
+    f = lib["nontemporal"]
+    for M, N, K, G in shapes(20000, 3):
+        assert not f(M, N, K, False), (M, N, K)
+        assert f(M, N, K, True) == (M <= 32 and N * (K // 2) >= 16 << 20), (M, N, K)
