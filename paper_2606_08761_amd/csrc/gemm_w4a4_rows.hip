@@ -24,15 +24,20 @@
 //     16 rows, weights past the cache): 8.9 us with two stages and several
 //     workgroups per CU, 9.3 with three, 9.7 with four, 10.4 with six and one
 //     workgroup per CU.
-//   * Activations are read 16 rows by 64 bytes per instruction (lane l: row
-//     l % 16, bytes 16 (l / 16)), whole 64-byte segments of a row; 32-row
-//     operands are put together from two such loads with v_permlane16_swap
-//     (lanes of a 32-row operand reading their 32 bytes directly touch twice as
-//     many segments per instruction: 4-15 % slower from 64 rows on).
+//   * Row-major operands (the activations, and weights of that layout) are read
+//     16 rows by 64 bytes per instruction (lane l: row l % 16, bytes
+//     16 (l / 16)), whole 64-byte segments of a row, which is the 16-row MFMA's
+//     operand; 32-row operands are put together from two such loads with
+//     v_permlane16_swap.  Lanes reading the 32 bytes of a 32-row operand directly
+//     touch twice as many segments per instruction: activations 4-15 % slower
+//     from 64 rows on; weights 2-5 % at 2 to 32 rows (8 rows, N = 8192,
+//     K = 28672: 27.2 -> 26.0 us; 32 rows, N = 8448: 60.6 -> 55.6).  The layout is
+//     a template argument: besides, tiled weights below 16 MB came out 3-7 %
+//     faster than with both in one kernel (16 rows and fewer, per channel, most).
 //   * Up to 16 rows: v_mfma_i32_16x16x64_i8, so no lane carries a row past 16:
 //     half the activation widening and half the MFMA time of the 32-row form.
-//     A lane's 32 weight bytes become the operands of two 16-column blocks by
-//     four v_permlane16_swap.
+//     A lane's 32 bytes of tiled weights become the operands of two 16-column
+//     blocks by four v_permlane16_swap.
 //   * Dequantization per stage as in the other kernels: the accumulator starts
 //     from 1.5 * 2^23, so the group (or 128-wide partial) sum reads as binary32,
 //     t = fma(D, s_w / 256, -1.5 * 2^23 s_w / 256), acc = fma(t, s_a, acc).
@@ -113,10 +118,10 @@ struct Form {
 // group's (several stages, one after the other in one wave), or the row's.
 enum RowsMode : int { kStage, kWhole, kChan };
 
-template <int RB, int CT, int NW, int PF, int OCC, bool NT, int MODE, bool DUMP, int QL>
+template <int RB, int CT, int NW, int PF, int OCC, bool WT, bool NT, int MODE, bool DUMP, int QL>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     const uint8_t* __restrict__ Aq, const uint16_t* __restrict__ sa, const uint8_t* __restrict__ Wq,
-    const uint16_t* __restrict__ sw, int M, int N, int K, int lg, int ng, uint16_t* __restrict__ Y, int wt,
+    const uint16_t* __restrict__ sw, int M, int N, int K, int lg, int ng, uint16_t* __restrict__ Y,
     const uint16_t* __restrict__ x, uint8_t* __restrict__ aq_out, uint16_t* __restrict__ sa_out,
     int32_t* __restrict__ P, int pm0, int pmr) {
     using F = Form<RB, CT>;
@@ -218,18 +223,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
     }
 
     // ---- ring of PF stages; offsets within 32 bits (operands below 4 GiB)
-    const uint32_t wbytes = wt ? static_cast<uint32_t>((N + 31) / 32) * static_cast<uint32_t>(nks) * 2048u
+    const uint32_t wbytes = WT ? static_cast<uint32_t>((N + 31) / 32) * static_cast<uint32_t>(nks) * 2048u
                                : static_cast<uint32_t>(N) * static_cast<uint32_t>(kb);
     const uint32_t abytes = static_cast<uint32_t>(M) * static_cast<uint32_t>(kb);
-    const int w_ss = wt ? 2048 : 64;
-    const uint32_t wj = wt ? 1024u : 16u;
+    const int w_ss = WT ? 2048 : 64;
     // a 32-column tile past the last one (odd tile count, CT = 2) starts at or past wbytes
-    uint32_t wv[CT];
+    uint32_t wv[2 * CT];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        const int t = ct * CT + c, col = n0 + 32 * c + l32;
-        if (wt) wv[c] = 32 * t < N ? static_cast<uint32_t>(t) * static_cast<uint32_t>(nks) * 2048u + 16u * lane : 0xFFFFFFF0u;
-        else wv[c] = col < N ? static_cast<uint32_t>(col) * static_cast<uint32_t>(kb) + 32u * lh : 0xFFFFFFF0u;
+    for (int c = 0; c < 2 * CT; ++c) {
+        const int t = ct * CT + c / 2, col = n0 + 16 * c + l16;
+        if (WT) wv[c] = 32 * t < N ? static_cast<uint32_t>(t) * static_cast<uint32_t>(nks) * 2048u + 1024u * (c & 1) + 16u * lane : 0xFFFFFFF0u;
+        else wv[c] = col < N ? static_cast<uint32_t>(col) * static_cast<uint32_t>(kb) + 16u * lq : 0xFFFFFFF0u;
     }
     uint32_t av[NA];
 #pragma unroll
@@ -247,15 +251,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
         // bytes of the stage inside a row: below 64 only in the last stage per channel
         const uint32_t lim = CH ? static_cast<uint32_t>(kb - s * 64) : 64u;
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            uint32_t v0 = wv[c], v1 = wv[c] == 0xFFFFFFF0u ? wv[c] : wv[c] + wj;
-            if (CH && !wt) {  // the tiled layout is zero padded
-                v0 = 32u * lh < lim ? v0 : 0xFFFFFFF0u;
-                v1 = 32u * lh + 16u < lim ? v1 : 0xFFFFFFF0u;
-            }
-            rw[j][2 * c] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(wr, v0, ws, NT ? NONTEMPORAL : 0));
-            rw[j][2 * c + 1] =
-                __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(wr, v1, ws, NT ? NONTEMPORAL : 0));
+        for (int c = 0; c < 2 * CT; ++c) {
+            const uint32_t v = (!CH || WT || 16u * lq < lim) ? wv[c] : 0xFFFFFFF0u;  // (the tiled layout is zero padded)
+            rw[j][c] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(wr, v, ws, NT ? NONTEMPORAL : 0));
         }
         if constexpr (!FUSE) {
             const auto ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(Aq), 0, live ? abytes : 0u, RSRC_FLAGS);
@@ -349,6 +347,15 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
         // 16-row operand of two
         constexpr int KM = RB == 0 ? 2 : 4;
         i32x4 af[RB == 0 ? 1 : RB][KM];
+        // 16 rows by 64 bytes in each of a, b <-> 32 rows by 32 bytes (the low and the high 16 of each half)
+        auto swap16 = [&](v4u& a, v4u& b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const auto t = __builtin_amdgcn_permlane16_swap(a[e], b[e], false, false);
+                a[e] = t[0];
+                b[e] = t[1];
+            }
+        };
         if constexpr (RB == 0) {
             v4u a;
             if constexpr (FUSE) a = *reinterpret_cast<const v4u*>(codes + s * 64 + 16 * lq);
@@ -358,13 +365,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
         } else {
 #pragma unroll
             for (int b = 0; b < RB; ++b) {
-                uint32_t h[2][4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const auto sw2 = __builtin_amdgcn_permlane16_swap(ra[j][2 * b][e], ra[j][2 * b + 1][e], false, false);
-                    h[0][e] = sw2[0];
-                    h[1][e] = sw2[1];
-                }
+                v4u h[2] = {ra[j][2 * b], ra[j][2 * b + 1]};
+                swap16(h[0], h[1]);
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) af[b][kk] = rfrag(h[kk >> 1][2 * (kk & 1)], h[kk >> 1][2 * (kk & 1) + 1]);
             }
@@ -388,14 +390,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
             for (int b = 0; b < (RB == 0 ? 2 : 1); ++b)
                 s1[b] = deq ? rh2f(wsc[g * COLS + 32 * c + col_of(b)]) * (1.0f / 256.0f) : 0.f;
             Acc d[NB];
+            v4u w[2] = {rw[j][2 * c], rw[j][2 * c + 1]};
+            if constexpr (WT == (RB == 0)) swap16(w[0], w[1]);
             if constexpr (RB == 0) {
-                uint32_t w[2][4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const auto sw2 = __builtin_amdgcn_permlane16_swap(rw[j][2 * c][e], rw[j][2 * c + 1][e], false, false);
-                    w[0][e] = sw2[0];
-                    w[1][e] = sw2[1];
-                }
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
                     d[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[0][0], rfrag(w[b][0], w[b][1]),
@@ -406,7 +403,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows_kernel(
                 i32x4 bw[4];
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {
-                    const v4u& v = rw[j][2 * c + (kk >> 1)];
+                    const v4u& v = w[kk >> 1];
                     bw[kk] = rfrag(v[2 * (kk & 1)], v[2 * (kk & 1) + 1]);
                 }
 #pragma unroll
@@ -513,7 +510,6 @@ struct Args {
     const uint16_t* sw;
     int64_t M, N, K, G;
     uint16_t* Y;
-    bool wt;
     const uint16_t* x;
     uint8_t* aq_out;
     uint16_t* sa_out;
@@ -530,11 +526,11 @@ int64_t rows_lds_bytes(int64_t K, int64_t G, int nw, bool fuse) {
     return front > red ? front : red;
 }
 
-template <int RB, int CT, int NW, int PF, int OCC, bool NT, int MODE, bool DUMP, int QL>
+template <int RB, int CT, int NW, int PF, int OCC, bool WT, bool NT, int MODE, bool DUMP, int QL>
 hipError_t launch_one(const Args& a) {
     using F = Form<RB, CT>;
     static std::atomic<uint64_t> lds_allowed{0};
-    const void* k = reinterpret_cast<const void*>(w4a4_rows_kernel<RB, CT, NW, PF, OCC, NT, MODE, DUMP, QL>);
+    const void* k = reinterpret_cast<const void*>(w4a4_rows_kernel<RB, CT, NW, PF, OCC, WT, NT, MODE, DUMP, QL>);
     const hipError_t e = allow_dynamic_lds(k, ROWS_LDS, lds_allowed);
     if (e != hipSuccess) return e;
     const int64_t lds = rows_lds_bytes<RB, CT>(a.K, a.G, NW, QL > 0);
@@ -544,10 +540,10 @@ hipError_t launch_one(const Args& a) {
         for (lg = 0; (int64_t{128} << lg) < a.G; ++lg) {
         }
     const dim3 grid(static_cast<unsigned>(((a.N + F::COLS - 1) / F::COLS + 7) / 8 * 8 * ((a.M + F::ROWS - 1) / F::ROWS)));
-    hipLaunchKernelGGL((w4a4_rows_kernel<RB, CT, NW, PF, OCC, NT, MODE, DUMP, QL>), grid, dim3(64 * NW),
+    hipLaunchKernelGGL((w4a4_rows_kernel<RB, CT, NW, PF, OCC, WT, NT, MODE, DUMP, QL>), grid, dim3(64 * NW),
                        static_cast<size_t>(lds), a.stream, a.Aq, a.sa, a.Wq, a.sw, static_cast<int>(a.M),
-                       static_cast<int>(a.N), static_cast<int>(a.K), lg, static_cast<int>(a.K / a.G), a.Y, a.wt ? 1 : 0,
-                       a.x, a.aq_out, a.sa_out, a.dump.P, a.dump.m0, a.dump.mr);
+                       static_cast<int>(a.N), static_cast<int>(a.K), lg, static_cast<int>(a.K / a.G), a.Y, a.x,
+                       a.aq_out, a.sa_out, a.dump.P, a.dump.m0, a.dump.mr);
     return hipGetLastError();
 }
 
@@ -556,17 +552,17 @@ hipError_t launch_one(const Args& a) {
 enum RowsForm : int { kR16, kR32, kR32x2, kR32x2w4, kR64, kR64w4 };
 
 // (DUMP: a shorter ring where the registers run out.)
-template <bool NT, int MODE, bool DUMP>
+template <bool WT, bool NT, int MODE, bool DUMP>
 hipError_t launch_form(RowsForm f, const Args& a) {
     if constexpr (MODE != kWhole) {  // more than 32 rows only
-        if (f == kR16) return launch_one<0, 1, 8, 2, 4, NT, MODE, DUMP, 0>(a);
-        if (f == kR32) return launch_one<1, 1, 8, 2, DUMP ? 2 : 4, NT, MODE, DUMP, 0>(a);
+        if (f == kR16) return launch_one<0, 1, 8, 2, 4, WT, NT, MODE, DUMP, 0>(a);
+        if (f == kR32) return launch_one<1, 1, 8, 2, DUMP ? 2 : 4, WT, NT, MODE, DUMP, 0>(a);
     }
-    if (f == kR32x2) return launch_one<1, 2, 8, 2, 2, NT, MODE, DUMP, 0>(a);
-    if (f == kR32x2w4) return launch_one<1, 2, 4, 2, 2, NT, MODE, DUMP, 0>(a);
+    if (f == kR32x2) return launch_one<1, 2, 8, 2, 2, WT, NT, MODE, DUMP, 0>(a);
+    if (f == kR32x2w4) return launch_one<1, 2, 4, 2, 2, WT, NT, MODE, DUMP, 0>(a);
     if constexpr (!NT) {
-        if (f == kR64) return launch_one<2, 2, 8, DUMP ? 1 : 2, 2, false, MODE, DUMP, 0>(a);
-        if (f == kR64w4) return launch_one<2, 2, 4, DUMP ? 1 : 2, 2, false, MODE, DUMP, 0>(a);
+        if (f == kR64) return launch_one<2, 2, 8, DUMP ? 1 : 2, 2, WT, false, MODE, DUMP, 0>(a);
+        if (f == kR64w4) return launch_one<2, 2, 4, DUMP ? 1 : 2, 2, WT, false, MODE, DUMP, 0>(a);
     }
     return hipErrorInvalidValue;
 }
@@ -665,24 +661,34 @@ bool rows_nontemporal(int64_t M, int64_t N, int64_t K, bool wt) {
     return wt && M <= 32 && N * (K / 2) >= ROWS_NT_BYTES;  // up to 32 rows: every weight is read by one workgroup
 }
 
+namespace {
+
+template <bool WT>
+hipError_t launch_layout(RowsForm f, const Args& a) {
+    const bool ch = a.G == a.K, whole = rows_whole(a.M, a.K, a.G);
+    if (a.dump.P) {
+        if (ch) return launch_form<WT, false, kChan, true>(f, a);
+        return whole ? launch_form<WT, false, kWhole, true>(f, a) : launch_form<WT, false, kStage, true>(f, a);
+    }
+    if constexpr (WT)
+        if (rows_nontemporal(a.M, a.N, a.K, true))
+            return ch ? launch_form<true, true, kChan, false>(f, a) : launch_form<true, true, kStage, false>(f, a);
+    if (ch) return launch_form<WT, false, kChan, false>(f, a);
+    return whole ? launch_form<WT, false, kWhole, false>(f, a) : launch_form<WT, false, kStage, false>(f, a);
+}
+
+}  // namespace
+
 hipError_t launch_gemm_rows(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw, int64_t M,
                             int64_t N, int64_t K, int64_t G, uint16_t* Y, hipStream_t stream, Dump dump, bool wt) {
     if (!rows_fits(M, N, K, G)) return hipErrorInvalidValue;
-    const Args a{Aq, sa, Wq, sw, M, N, K, G, Y, wt, nullptr, nullptr, nullptr, dump, stream};
+    const Args a{Aq, sa, Wq, sw, M, N, K, G, Y, nullptr, nullptr, nullptr, dump, stream};
     const RowsForm f = rows_form(M, N, K, G);
-    const bool ch = G == K, whole = rows_whole(M, K, G);
-    if (dump.P) {
-        if (!ch) {  // sums are added atomically into a zeroed window
-            const hipError_t e = launch_fill_i32(dump.P, static_cast<int64_t>(dump.mr) * N * (K / G), 0, stream);
-            if (e != hipSuccess) return e;
-        }
-        if (ch) return launch_form<false, kChan, true>(f, a);
-        return whole ? launch_form<false, kWhole, true>(f, a) : launch_form<false, kStage, true>(f, a);
+    if (dump.P && G != K) {  // sums are added atomically into a zeroed window (per channel: stored)
+        const hipError_t e = launch_fill_i32(dump.P, static_cast<int64_t>(dump.mr) * N * (K / G), 0, stream);
+        if (e != hipSuccess) return e;
     }
-    if (rows_nontemporal(M, N, K, wt))
-        return ch ? launch_form<true, kChan, false>(f, a) : launch_form<true, kStage, false>(f, a);
-    if (ch) return launch_form<false, kChan, false>(f, a);
-    return whole ? launch_form<false, kWhole, false>(f, a) : launch_form<false, kStage, false>(f, a);
+    return wt ? launch_layout<true>(f, a) : launch_layout<false>(f, a);
 }
 
 // The one-row linear on tiled weights with the quantizer in the prologue.
@@ -694,15 +700,15 @@ bool rows_fused_fits(int64_t M, int64_t N, int64_t K, int64_t G) {
 namespace {
 template <int QL>
 hipError_t launch_fused_g(const Args& a, bool nt) {
-    if (a.dump.P) return launch_one<0, 1, 8, 2, 4, false, kStage, true, QL>(a);
-    return nt ? launch_one<0, 1, 8, 2, 4, true, kStage, false, QL>(a) : launch_one<0, 1, 8, 2, 4, false, kStage, false, QL>(a);
+    if (a.dump.P) return launch_one<0, 1, 8, 2, 4, true, false, kStage, true, QL>(a);
+    return nt ? launch_one<0, 1, 8, 2, 4, true, true, kStage, false, QL>(a) : launch_one<0, 1, 8, 2, 4, true, false, kStage, false, QL>(a);
 }
 }  // namespace
 
 hipError_t launch_rows_fused(const uint16_t* x, const uint8_t* Wt, const uint16_t* sw, int64_t N, int64_t K, int64_t G,
                              uint16_t* Y, uint8_t* Aq, uint16_t* sa, hipStream_t stream, Dump dump) {
     if (!rows_fused_fits(1, N, K, G)) return hipErrorInvalidValue;
-    const Args a{nullptr, nullptr, Wt, sw, 1, N, K, G, Y, true, x, Aq, sa, dump, stream};
+    const Args a{nullptr, nullptr, Wt, sw, 1, N, K, G, Y, x, Aq, sa, dump, stream};
     if (dump.P) {
         const hipError_t e = launch_fill_i32(dump.P, static_cast<int64_t>(dump.mr) * N * (K / G), 0, stream);
         if (e != hipSuccess) return e;

@@ -25,7 +25,7 @@ FLAGS = {
     "w4a4_decode_kernel": (3, 4),
     "w4a4_gemv_kernel": (2, None),
     "w4a4_gemv_tiled_kernel": (0, None),
-    "w4a4_rows_kernel": (7, None),
+    "w4a4_rows_kernel": (8, None),
 }
 
 
