@@ -691,10 +691,18 @@ hipError_t launch_gemm_rows(const uint8_t* Aq, const uint16_t* sa, const uint8_t
     return wt ? launch_layout<true>(f, a) : launch_layout<false>(f, a);
 }
 
-// The one-row linear on tiled weights with the quantizer in the prologue.
+// The one-row linear on tiled weights with the quantizer in the prologue, where
+// that is the faster way: every workgroup quantizes all of x, beside the loads
+// of its weights, against a launch and a round trip of the codes.
+// MI355X, G = 128, us, fused / quantizer and GEMM: N = 8192, K = 2048 5.8 / 7.1;
+// N = 57344, K = 8192 38.2 / 38.8; N = 28672, K = 14336 37.1 / 36.8, K = 28672
+// 70.4 / 68.1; N = 256, K = 28672 15.6 / 15.4, K = 57344 27.8 / 25.0 (longer K
+// the same).  G = 512 (a group's maximum over all lanes) loses earlier where
+// workgroups come in several rounds: N = 14336, K = 2048 6.9 / 8.3, but
+// N = 28672 11.2 / 10.8 and N = 57344, K = 4096 24.4 / 22.6.
 bool rows_fused_fits(int64_t M, int64_t N, int64_t K, int64_t G) {
-    return M == 1 && N >= 1 && (G == 128 || G == 256 || G == 512) && G < K &&
-           rows_lds_bytes<0, 1>(K, G, 8, true) <= ROWS_LDS;
+    return M == 1 && N >= 1 && (G == 128 || G == 256 || (G == 512 && N <= 16384)) && G < K &&
+           (K <= 16384 || cdiv(N, 32) * K <= (int64_t{1} << 18)) && rows_lds_bytes<0, 1>(K, G, 8, true) <= ROWS_LDS;
 }
 
 namespace {

@@ -35,6 +35,7 @@ def lib():
     return {"plan": lambda M, N, K, G, split, wt=False: (lambda p: (p.kernel, p.splits))(plan(M, N, K, G, split, False, wt)),
             "workspace": fn("_ZN5apex422splitk_workspace_bytesEllll", I),
             "rows_fits": fn("_ZN5apex49rows_fitsEllll", b),
+            "fused": fn("_ZN5apex415rows_fused_fitsEllll", b),
             "nontemporal": _nontemporal(L)}
 
 
@@ -87,3 +88,18 @@ def test_few_row_kernel_streams_tiled_weights_only(lib):
     for M, N, K, G in shapes(20000, 3):
         assert not f(M, N, K, False), (M, N, K)
         assert f(M, N, K, True) == (M <= 32 and N * (K // 2) >= 16 << 20), (M, N, K)
+
+
+def test_fused_row_is_bounded(lib):
+    """One row on tiled weights: every workgroup quantizes all of x, so the fused
+    form ends where a separate quantizer is the faster way (long K; at G = 512
+    many columns), and at the groups that a wave holds."""
+    f = lib["fused"]
+    for G in (128, 256, 512):
+        assert f(1, 8192, 8192, G) and f(1, 16384, 16384, G) and f(1, 64, 40960, G)
+        assert not f(1, 8192, 16384 + G, G) and not f(1, 2048, 57344, G) and not f(2, 8192, 8192, G)
+        assert f(1, 57344, 8192, G) == (G < 512)
+    assert not f(1, 8192, 8192, 1024) and not f(1, 512, 512, 512)
+    for _, N, K, G in shapes(20000, 4):
+        if f(1, N, K, G):
+            assert G in (128, 256, 512) and G < K and (K <= 16384 or N * K <= 33 << 18), (N, K, G)
