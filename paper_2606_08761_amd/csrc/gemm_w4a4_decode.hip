@@ -723,15 +723,30 @@ int64_t decode_split_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t G)
 }
 
 // At G >= 128 or per channel the form competes with the kernel of
-// gemm_w4a4_rows.hip, which keeps several workgroups per CU: it is kept for few
-// tiles of many stages, and for a few tiles past one full round (MI355X, 16
-// rows, K = 28672, us: N = 1024 12.6 against 14.0, but N = 2560 19.0 against
-// 18.8, N = 5120 26.9 against 20.7, N = 12288 46.6 against 40.6, N = 28672
-// 92.8 against 79.7).
+// gemm_w4a4_rows.hip, one choice for both weight layouts, whose results are the
+// same bits.  Measured over 2 to 32 rows, N = 512 .. 28672, K = 16384 .. 57344,
+// G = 128 .. 1024 and per channel; this form / the other in us, tiled weights,
+// row-major:
+//   * Up to cus/4 tiles: this one (16 rows, N = 1024: K = 16384 11.1 / 8.9, 12.6 /
+//     13.5; K = 24576 11.9 / 12.1, 13.5 / 19.5; K = 57344 15.6 / 33.5, 16.8 / 51.6).
+//   * Up to one tile per CU: what the idle CUs take over, (1 - tiles / cus) of a
+//     workgroup's stages, against a fixed cost of about 11 us (the clear, the
+//     count and the addition): at 150 to 170 stages both take the same on tiled
+//     weights, at 100 to 150 on row-major ones.  N = 2560, 16 rows: K = 24576
+//     18.0 / 16.8, 20.1 / 24.6; K = 28672 19.1 / 19.1, 21.4 / 27.8; K = 57344
+//     26.3 / 35.2, 30.3 / 51.6.  4 rows, K = 28672: 17.3 / 16.4, 19.0 / 20.3.
+//   * Past it, up to cus/8 tiles in the second round (16 rows, N = 8448: K = 24576
+//     32.5 / 32.4, 38.7 / 47.7), and at 9 to 16 rows of K >= 28672 up to cus/4 in
+//     any round (N = 10240: K = 28672 38.8 / 38.7, 47.4 / 55.0; N = 17408,
+//     K = 57344 109 / 112, 142 / 166; but 4 rows, N = 17408, K = 28672: 56.1 / 47.7).
 bool decode_split_pays(int64_t M, int64_t N, int64_t K, int64_t G) {
     if (decode_split_workspace_bytes(M, N, K, G) == 0) return false;
-    const int64_t tiles = (N + COLS - 1) / COLS, cus = device_cu_count();
-    return (G < 128 && G != K) || tiles <= cus / 4 || (tiles > cus && tiles - cus <= cus / 8);
+    if (G < 128 && G != K) return true;
+    const int64_t tiles = (N + COLS - 1) / COLS, cus = device_cu_count(), n = kstages(K);
+    if (tiles <= cus / 4) return true;
+    if (tiles <= cus) return n * (cus - tiles) > (M > 8 ? 150 : 170) * cus;
+    if (M > 8 && M <= 16 && n >= 224) return tiles % cus <= cus / 4;
+    return tiles - cus <= cus / 8;
 }
 
 hipError_t launch_gemm_decode(const uint8_t* Aq, const uint16_t* sa, const uint8_t* Wq, const uint16_t* sw,

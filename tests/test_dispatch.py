@@ -103,3 +103,17 @@ def test_fused_row_is_bounded(lib):
     for _, N, K, G in shapes(20000, 4):
         if f(1, N, K, G):
             assert G in (128, 256, 512) and G < K and (K <= 16384 or N * K <= 33 << 18), (N, K, G)
+
+
+# (M, N, K, stream-K or not) at G = 128 on 256 CUs, on both sides of each line
+SPLIT_LINES = [(16, 2048, 16384, True), (16, 2560, 24576, False), (9, 2560, 28672, True), (8, 2560, 28672, False),
+               (8, 2560, 32768, True), (32, 3072, 32768, True), (32, 3584, 32768, False), (2, 3584, 57344, True),
+               (32, 8192, 57344, False), (2, 9216, 24576, True), (16, 10240, 24576, False), (16, 10240, 28672, True),
+               (17, 10240, 28672, False), (9, 17408, 28672, True), (8, 17408, 28672, False), (16, 12288, 57344, False)]
+
+
+def test_stream_k_where_it_pays(lib):
+    for M, N, K, split in SPLIT_LINES:
+        for wt in (False, True):
+            if M > 2 or not wt:  # two rows on tiled weights: the dot-product kernel
+                assert (lib["plan"](M, N, K, 128, True, wt) == (DECODE_SPLIT, 1)) == split, (M, N, K, wt)
