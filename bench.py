@@ -418,16 +418,17 @@ def decode_split_mode(reps: int = 40, rounds: int = 6):
                            "ratio": round(b / a, 3)}
                     rows.append(row)
                     print(json.dumps(row), flush=True)
-    lines = ["# Few-row GEMM: round robin against the stream-K form", "",
+    lines = ["# Few-row GEMM: without a workspace against the stream-K form", "",
              "Command (run from the repository root on one MI355X):", "", "```",
              "python3 bench.py --mode decode_split", "```", "",
              f"Each shape: {reps} calls captured in a graph per form, the two graphs replayed alternately "
              f"{rounds} times (median per call), weights rotated over >= {ROTATE_BYTES >> 20} MB of copies, "
-             "random codes and scales. Round robin: the entry without a workspace (apex4_w4a4_gemm_tiled for "
-             "G = 128 on tiled weights, apex4_w4a4_gemm for G = 32). Workspace: the same entry with the workspace "
-             "the size query returns; it runs the stream-K form where the plan says decode_split, otherwise the "
-             "same kernel as round robin (ratio ~1 there is the run-to-run spread).", "",
-             "| G | K | N | M | plan (workspace entry) | workspace bytes | round robin µs | workspace µs | ratio |",
+             "random codes and scales. No workspace: apex4_w4a4_gemm_tiled for G = 128 on tiled weights (the few-row "
+             "kernel of gemm_w4a4_rows.hip), apex4_w4a4_gemm for G = 32 (the persistent kernel, its tiles round "
+             "robin). Workspace: the same entry with the workspace the size query returns; it runs the stream-K "
+             "form of the persistent kernel where the plan says decode_split, otherwise the same kernel as without "
+             "(ratio ~1 there is the run-to-run spread).", "",
+             "| G | K | N | M | plan (workspace entry) | workspace bytes | no workspace µs | workspace µs | ratio |",
              "|---|---|---|---|---|---|---|---|---|"]
     for r_ in rows:
         lines.append(f"| {r_['G']} | {r_['K']} | {r_['N']} | {r_['M']} | {r_['plan_ws']} | {r_['workspace_bytes']} | "
@@ -698,11 +699,17 @@ def summarize_sq_variants(paths, cmds):
         f.write("\n".join(lines) + "\n")
 
 
-# (label, M, N, K, G, tiled, kernel instantiation the plan picks: MROWS, ring depth, groups per stage)
-DECODE_SQ = [("G=32, K=28672: the mixed configuration's down projection", 16, 8192, 28672, 32, False, "<16, 4, 4,"),
-             ("G=128, N=K=8192, tiled weights", 16, 8192, 8192, 128, True, "<16, 6, 1,"),
-             ("G=128, N=28672, K=8192, tiled weights, activations staged in LDS", 32, 28672, 8192, 128, True,
-              "<32, 6, 1,")]
+# (label, M, N, K, G, tiled, kernel instantiation the plan picks, its MFMA): the
+# persistent kernel (rows, ring depth, groups per stage), and the few-row kernel
+# (32-row blocks or 0 for 16 rows, 32-column tiles, waves, ring depth, ...)
+DECODE_SQ = [("G=32, K=28672: the mixed configuration's down projection", 16, 8192, 28672, 32, False,
+              "w4a4_decode_kernel<16, 4, 4,", "v_mfma_i32_32x32x32_i8"),
+             ("G=128, N=K=8192, tiled weights: 16 rows by 32 columns", 16, 8192, 8192, 128, True,
+              "w4a4_rows_kernel<0, 1, 8, 2,", "v_mfma_i32_16x16x64_i8"),
+             ("G=128, N=28672, K=8192, tiled weights: 32 rows by 64 columns, four waves", 32, 28672, 8192, 128, True,
+              "w4a4_rows_kernel<1, 2, 4, 2,", "v_mfma_i32_32x32x32_i8"),
+             ("G=128, N=K=8192, tiled weights: 64 rows by 64 columns", 72, 8192, 8192, 128, True,
+              "w4a4_rows_kernel<2, 2, 8, 2,", "v_mfma_i32_32x32x32_i8")]
 
 
 def decode_sq_mode(reps: int = 5):
@@ -713,7 +720,7 @@ def decode_sq_mode(reps: int = 5):
     import paper_2606_08761_amd as pk
     from paper_2606_08761_amd import workloads as wl
     dev = torch.device("cuda", 0)
-    for (label, Md, Nd, Kd, Gd, tiled, _) in DECODE_SQ:
+    for (label, Md, Nd, Kd, Gd, tiled, _, _) in DECODE_SQ:
         r = wl.rng_for("decode", 11, Md * 7 + Nd + Kd + Gd)
         Wq = torch.from_numpy(wl.random_codes(r, Nd, Kd)).to(dev)
         W = pk.apex4_tile_weights(Wq) if tiled else Wq
@@ -735,15 +742,17 @@ def decode_sq_mode(reps: int = 5):
 def summarize_decode_sq(paths, cmds):
     """profiles/decode_sq.md: where the SIMD cycles of the few-row kernel go
     (bench.py --mode decode_sq)."""
-    lines = ["# Few-row GEMM (M = 16 and 32): SQ counters", "",
+    lines = ["# Few-row GEMM (M = 16, 32 and 72): SQ counters", "",
              "Commands (run from the repository root on one MI355X):", "", "```", cmds, "```", "",
-             "Means over the launches of each case. The kernel fills the CUs with one 8-wave workgroup each; "
-             "shares are of the kernel's cycles per SIMD.", ""]
-    for (label, Md, Nd, Kd, Gd, tiled, key) in DECODE_SQ:
-        c = _sq_means(paths, lambda n, key=key: "w4a4_decode_kernel" in n and key in n)
+             "Means over the launches of each case (the first reads the weights from HBM, the others those below "
+             "256 MB from the Infinity Cache). The persistent kernel (G = 32) fills the CUs with one 8-wave "
+             "workgroup each, the few-row kernel keeps several where there are as many; shares are of the kernel's "
+             "cycles per SIMD.", ""]
+    for (label, Md, Nd, Kd, Gd, tiled, key, mfma) in DECODE_SQ:
+        c = _sq_means(paths, lambda n, key=key: key in n)
         if "GRBM_GUI_ACTIVE" in c and "SQ_INSTS_MFMA" in c:
             lines += [f"## M={Md} N={Nd} K={Kd} {label}", ""]
-            lines += _sq_section(c, f"w4a4_decode_kernel{key.rstrip(',')}...>", "v_mfma_i32_32x32x32_i8") + [""]
+            lines += _sq_section(c, f"{key} ...>", mfma) + [""]
     with open(os.path.join(ROOT, "profiles", "decode_sq.md"), "w") as f:
         f.write("\n".join(lines) + "\n")
 
@@ -1189,6 +1198,9 @@ def _decode_kernel_role(name: str):
     m = re.search(r"w4a4_gemv(?:_tiled)?_kernel<(true|false)", name)
     if m:
         return "fused" if m.group(1) == "true" else "gemv"
+    m = re.search(r"w4a4_rows_kernel<[^>]*, (\d+)>", name)
+    if m:
+        return "decode" if m.group(1) == "0" else "fused"
     if "w4a4_decode_kernel" in name:
         return "decode"
     if is_tiled_gemm(name):
