@@ -231,7 +231,8 @@ int apex4_w4a4_gemm_tiled(const uint8_t* A_q, const void* s_a,
  * offline).  Y and the work buffers end up exactly as after
  * apex4_quantize_act(x) into the work buffers followed by apex4_w4a4_gemm on
  * the same stream.  For one row (M = 1) and G in {32, 64, 128, 256, 512}
- * (G < K) this is one fused kernel that quantizes x in its prologue;
+ * (G < K) this is one fused kernel that quantizes x in its prologue, where
+ * that is the faster way (its size rule: every workgroup quantizes all of x);
  * otherwise the two kernels are enqueued in that order.
  *
  *   x [M, K] binary16, W_q [N, K/2], s_w [N, K/G]  (device, read-only);

@@ -1288,6 +1288,13 @@ double tile_cost_us(int64_t M, int64_t N, int64_t K, int64_t G, int S) {
 // kernels with a workspace, 1.5 to 1.8 times without (64 rows, N = 28672,
 // K = 8192, G = 256: 40 against 38 us; 200 rows, N = 28672, K = 2048: 34 against
 // 32; 64 rows, N = 3072, K = 20480, G = 512: 26.5 against 22.6 split over K).
+// Row-major weights take the same kernel, so that both layouts give the same
+// bits, though the few-row kernel loses more by that layout than the tile
+// kernels: over 639 shapes of 33 .. 255 rows, all groups, its choice makes the
+// calls 0.63 of the tile kernels' time on tiled weights (2 % of the shapes more
+// than 5 % slower, at most 1.29: 224 rows, N = 47168, K = 26240) and 0.72 on
+// row-major ones (7 %, at most 1.49: per channel, 160 rows, N = 44704, K = 11520
+// 154 -> 229 us; 72 rows, N = 320, K = 18944 21.1 -> 28.4).
 bool rows_take(int64_t M, int64_t N, int64_t K, int64_t G, int S) {
     return rows_fits(M, N, K, G) && (M <= 32 || rows_cost_us(M, N, K, G) < tile_cost_us(M, N, K, G, S));
 }

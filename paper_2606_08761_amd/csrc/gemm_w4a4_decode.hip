@@ -3,6 +3,8 @@
 // Same result as the tiled kernel (APEX4 Sec. 3.2.1, Eq. group_decomposition),
 // organised for the memory-bound regime, where the weights are streamed from HBM
 // once and the HBM queue is kept full.
+// It serves groups of 32 and 64; at G >= 128 and per channel its stream-K form
+// does where decode_split_pays says so, and gemm_w4a4_rows.hip the rest.
 //   * Work unit: 32 output columns ("tile") by every row.  Workgroups are
 //     persistent (at most one per CU) and walk the tiles blockIdx.x,
 //     blockIdx.x + gridDim.x, ...  Their 8 waves split the 128-wide K stages

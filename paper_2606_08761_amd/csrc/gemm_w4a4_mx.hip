@@ -312,7 +312,10 @@ __global__ __launch_bounds__(512, 1) void w4a4_gemm_mx_kernel(
     // products of stage s, after those of its first row block, so that the LDS
     // writes do not come before the operand reads of all waves at once (M = 2048,
     // N = K = 8192, G = 128: 121.2 -> 116.0 us; M = 3001, N = 10240, K = 4096:
-    // 123.1 -> 115.1).  Chunks loaded straight into LDS, three stages deep: 2-4 %
+    // 123.1 -> 115.1; G = 64 129.4 -> 127.1 and 127.1 -> 122.3; G = 32 within 1 %
+    // there, 138.8 -> 139.0 and 135.2 -> 134.5.  Over 120 seeded shapes of 1 ..
+    // 4096 rows, N = 256 .. 20480, K = 512 .. 16384: 7-10 % on average at each G
+    // where the GEMM takes 40 us and more).  Chunks loaded straight into LDS, three stages deep: 2-4 %
     // faster still with 256-row tiles, 14 % slower with 128-row ones (M = 1024).
     load(0);
     store(0);
